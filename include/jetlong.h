@@ -334,11 +334,12 @@ int jl_bifocal_decode(const void* q, const void* k_cache, const void* v_cache,
  * hipMalloc).  Same arguments and results, bit for bit, without the
  * workspace: the split states and the fp32 cos/sin table live in one fixed
  * device array that the library holds on each device it runs on until the
- * process ends (88 MiB: the table of positions [0, 131072) and 24 MiB of
+ * process ends (93 MiB: the table of positions [0, 131072) and 29 MiB of
  * states).  No call allocates or frees device memory.
- *   max_len > 131072, or split states above 24 MiB
- *   (jl_decode_workspace_bytes(B, Hq, Hkv, max_len, 128) > 25165824)
- *     -> JL_ERR_UNSUPPORTED, checked on the host before any device work.
+ *   max_len > 131072, or more than 24 MiB of states counted as
+ *   B * Hq * n * 528 bytes with n = min(128, ceil(max_len / 16)) up to B = 64
+ *   and n = min(ceil(256 / (B * ceil(Hkv / 4))), 128, ceil(max_len / 16))
+ *   beyond -> JL_ERR_UNSUPPORTED, checked on the host before any device work.
  * The first call on a device for a given rope_theta builds the table and
  * waits for it on `stream` (make that call outside graph capture); later
  * calls with that theta launch the two decode kernels only.  Every call on a

@@ -8,10 +8,10 @@
 // L = kv_len[b] (Eq. (2)), computed on the device, so one launch serves a
 // ragged batch whose sequences have different G.
 //
-// Split-K: workgroup (b, group of up to 4 kv heads, split) streams every
-// ns_b-th 16-key step of sequence b, two waves per kv head; ns_b follows the
-// sequence's length (split_work), so a ragged batch keeps every CU busy for
-// about the same time.  The Sec. 4.5 frequency map replaces the remote
+// Split-K: workgroup (group of up to 4 kv heads, w) streams the w-th equal
+// part of the batch's 16-key steps, two waves per kv head, whatever sequences
+// that part spans (SplitRange), so a ragged batch keeps every CU busy for
+// the same time.  The Sec. 4.5 frequency map replaces the remote
 // rotation by one at unchanged positions with rescaled frequencies.  The g query
 // heads of a kv head are rotated twice (base and remote) and placed in the 16
 // columns of a v_mfma_f32_16x16x32_bf16 B operand: columns 0..7 hold
@@ -22,6 +22,8 @@
 // window state and the remote-only state of Sec. 3.3.  Each split merges its
 // head's two view states with the max-shifted, linear-space rule of Eq. (7)
 // in fp32, and the reduce kernel merges the splits' states the same way.
+#include <algorithm>
+#include <climits>
 #include <mutex>
 
 #include "jl_device.h"
@@ -38,12 +40,16 @@ constexpr int kDecBufBytes = 2 * kDecImgBytes + 1024;  // K, V and the step's tw
 constexpr int kDecOffTab = kDecBufs * kDecBufBytes;
 constexpr int kDecTabRow = kHalf * 8 + 16;  // one offset row: 64 (cos, sin) pairs + 16 B pad
 constexpr int kDecOffTab2 = kDecOffTab + kDecTile * kDecTabRow;    // + 16 offset rows (base)
-constexpr int kDecOffDummy = kDecOffTab2 + kDecTile * kDecTabRow;  // + 16 offset rows (freq map)
+constexpr int kDecOffDummy = kDecOffTab2 + kDecTile * kDecTabRow;  // + 16 offset rows (freq map),
+                                                                   // or the raw query rows
 constexpr int kDecOffPages = kDecOffDummy + 1024;                  // + landing slot for padding copies
 constexpr int kDecPageCap = 2048;  // paged caches: page indices of up to this many steps in LDS
 constexpr int kDecSmem = kDecOffPages + kDecPageCap * 4;
 constexpr int kDecCopies = 5;  // copies per step of wave 0: four K/V (padded to a fixed count) + rows
-constexpr int kStateFloats = 132;  // m, l, the split count (int bits), pad, O[128]
+constexpr int kStateFloats = 132;  // m, l, the split count (int bits, B = 1), pad, O[128]
+// What a workgroup pays for each further sequence it works on (refilling the
+// copy pipeline, merging and writing the states), in steps of the copy stream.
+constexpr int kDecSegCost = 4;
 
 struct DecodeArgs {
   const uint16_t* q;
@@ -58,101 +64,141 @@ struct DecodeArgs {
   // caches [B][max_len][Hkv][128]
   const int32_t* block_table;
   int max_pages, n_pages, page_shift;
-  int chunk, n_split, n_hgroups;  // n_split: split slots per (b, kv-head group)
-  int balanced;  // split counts from the actual lengths (B <= 64), else from max_len
+  int n_hgroups;  // groups of up to 4 kv heads
+  int n_wg;       // workgroups per kv-head group
+  int n_slots;    // state slots (see SplitRange)
   // frequency-interpolation remote map (Sec. 4.5): omega_i and the ramp
   // gamma_i of each frequency pair; every workgroup forms the cos/sin rows it
   // needs from them and its sequence's length
   double fomega[kHalf];
   double fgamma[kHalf];
-  int n_target;  // balanced: workgroups of the grid (one wave of them fills the GPU)
   int w_pre, w0;
   float q_scale;
 };
 
 __device__ inline int clamp_len(int n, int max_len) { return n < 1 ? 1 : (n > max_len ? max_len : n); }
 
-__device__ inline int wave_sum(int x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-  return x;
-}
-
-__device__ inline int wave_max(int x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = max(x, __shfl_xor(x, o));
-  return x;
-}
-
-// 16-key steps of sequence `lane` (0 for lanes past B)
-__device__ inline int lane_steps(const DecodeArgs& a, int lane) {
-  return lane < a.B ? (clamp_len(a.kv_lens[lane], a.max_len) + kDecTile - 1) / kDecTile : 0;
-}
-
-// Balanced splits of a ragged batch (one lane per sequence, s = its steps):
-// every split takes at most u steps, u the smallest count for which the
-// busy workgroups, n_hgroups * sum_b min(n_split, ceil(s_b / u)), fit the
-// grid's n_target slots; the bisection starts from the bounds
-//   ceil(total / S) <= u <= ceil(total / (S - B))   (S = n_target / n_hgroups)
-// since sum_b ceil(s_b / u) lies between total / u and total / u + B.
-__device__ inline int balanced_unit(const DecodeArgs& a, int s) {
-  const int S = a.n_target / a.n_hgroups;  // >= B
-  const int smax = wave_max(s);
-  if (a.B == 1) return max(1, (smax + S - 1) / S);
-  const int total = wave_sum(s);
-  int lo = max(1, (total + S - 1) / S);
-  int hi = S > a.B ? min(smax, (total + S - a.B - 1) / (S - a.B)) : smax;
-  lo = min(lo, hi);
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    const int c = wave_sum(s > 0 ? min(a.n_split, (s + mid - 1) / mid) : 0);
-    if (c <= S) hi = mid; else lo = mid + 1;
-  }
-  return lo;
-}
-
-// What workgroup bid does: sequence b, kv-head group, split `split` of ns
-// (ns == 0: nothing, the workgroup exits).  Balanced grids list, per
-// sequence, its ns_b * n_hgroups workgroups one after another.
-struct SplitWork {
-  int b, hgroup, split, ns;
+// The batch's 16-key steps are one list, sequence after sequence, and
+// workgroup w of a kv-head group takes an equal range of it: about one
+// workgroup per CU, all finishing together whatever the lengths are.  A range
+// may end one sequence and begin others; each (workgroup, sequence) pair is a
+// split.  A batch's sequences are followed by kDecSegCost empty steps each in
+// the list, so that a workgroup with more splits gets fewer keys.  The splits
+// of one range are in list order, so w + b names a split: it is the slot of
+// its states, and a sequence's slots are consecutive.  (Split counts rounded
+// up per sequence, ceil(steps / u) of them, left the longest workgroup 10%
+// above the mean at 32 sequences of 0.5K to 16K keys, and above 64 sequences
+// every one was cut by max_len.)
+//
+// The range only counts a split's steps.  Where a sequence spans several whole
+// ranges, their workgroups interleave: of n of them, the i-th takes every n-th
+// step from its i-th on, so that at any moment they stream one narrow window
+// of the cache.  Each streaming its own run of steps instead took 3% longer at
+// 128K keys and 4% at 8 sequences of 32K to 128K.
+struct SplitRange {
+  int b;        // first sequence
+  int off;      // first step of it (past its last one: inside its empty steps)
+  int left;     // steps of the list, empty ones included; 0: nothing to do
+  int n_wg;     // workgroups with a range
+  uint32_t pos; // list entry of sequence b's first step
+  uint32_t q, r;  // entries per range, and ranges (the first ones) with one more; q = 0: a list
+                  // too long for 32 bits, whose splits all take runs of steps
 };
 
-__device__ inline SplitWork split_work(const DecodeArgs& a, int bid) {
-  SplitWork w;
-  if (!a.balanced) {
-    w.split = bid % a.n_split;
-    const int t0 = bid / a.n_split;
-    w.hgroup = t0 % a.n_hgroups;
-    w.b = t0 / a.n_hgroups;
-    const int s_all = (clamp_len(a.kv_lens[w.b], a.max_len) + kDecTile - 1) / kDecTile;
-    w.ns = min(a.n_split, s_all);
-    if (w.split >= w.ns) w.ns = 0;
-    return w;
-  }
+__device__ inline int seq_steps(const DecodeArgs& a, int b) {
+  return (clamp_len(a.kv_lens[b], a.max_len) + kDecTile - 1) / kDecTile;
+}
+
+// Ranges of a list of V < 2^32 entries, and where range w begins
+__device__ inline uint32_t set_ranges(SplitRange& s, int n_wg, uint32_t V, int w) {
+  s.n_wg = min((uint32_t)n_wg, V);
+  s.q = V / (uint32_t)s.n_wg;
+  s.r = V - s.q * s.n_wg;
+  s.left = w < s.n_wg ? (int)(s.q + ((uint32_t)w < s.r ? 1 : 0)) : 0;
+  return s.q * w + min((uint32_t)w, s.r);
+}
+// The workgroup whose range holds list entry x
+__device__ inline int range_of(const SplitRange& s, uint32_t x) {
+  const uint32_t head = s.r * (s.q + 1);
+  return (int)(x < head ? x / (s.q + 1) : s.r + (x - head) / s.q);
+}
+
+__device__ inline SplitRange split_range(const DecodeArgs& a, int w) {
+  SplitRange s;
   const int lane = threadIdx.x & 63;
-  const int s = lane_steps(a, lane);
-  const int u = balanced_unit(a, s);
-  const int ns = s > 0 ? min(a.n_split, (s + u - 1) / u) : 0;
-  int incl = ns * a.n_hgroups;  // inclusive scan over the sequences
+  if (a.B == 1) {
+    s.b = 0;
+    s.pos = 0;
+    s.off = (int)set_ranges(s, a.n_wg, (uint32_t)seq_steps(a, 0), w);
+    return s;
+  }
+  if (a.B <= 64) {  // one lane per sequence, every wave for itself
+    const int v = lane < a.B ? seq_steps(a, lane) + kDecSegCost : 0;
+    int incl = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int x = __shfl_up(incl, o);
+      if (lane >= o) incl += x;
+    }
+    const int x0 = (int)set_ranges(s, a.n_wg, (uint32_t)__builtin_amdgcn_readlane(incl, 63), w);
+    const int b = min((int)__popcll(__ballot(incl <= x0)), a.B - 1);
+    s.b = __builtin_amdgcn_readfirstlane(b);
+    s.pos = (uint32_t)__builtin_amdgcn_readlane(incl - v, s.b);
+    s.off = x0 - (int)s.pos;
+    return s;
+  }
+  // larger batches: one thread per run of ceil(B / threads) sequences
+  __shared__ unsigned long long s_sum[kDecWaves];
+  __shared__ int s_at[3];
+  const int tid = threadIdx.x, wave = tid >> 6;
+  const int per = (a.B + kDecThreads - 1) / kDecThreads;
+  const long long b0 = (long long)tid * per;
+  const int b1 = (int)min((long long)a.B, b0 + per);
+  unsigned long long v = 0;
+  for (long long b = b0; b < b1; ++b) v += seq_steps(a, (int)b) + kDecSegCost;
+  unsigned long long incl = v;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const int x = __shfl_up(incl, o);
+    const unsigned long long x = __shfl_up(incl, o);
     if (lane >= o) incl += x;
   }
-  const int b = __popcll(__ballot(lane < a.B && incl <= bid));
-  w.b = min(b, a.B - 1);
-  const int incl_b = __shfl(incl, w.b);
-  const int ns_b = __shfl(ns, w.b);
-  const int r = bid - (incl_b - ns_b * a.n_hgroups);
-  w.ns = b < a.B ? ns_b : 0;
-  w.hgroup = w.ns > 0 ? r / ns_b : 0;
-  w.split = w.ns > 0 ? r - w.hgroup * ns_b : 0;
-  w.b = __builtin_amdgcn_readfirstlane(w.b);
-  w.ns = __builtin_amdgcn_readfirstlane(w.ns);
-  w.hgroup = __builtin_amdgcn_readfirstlane(w.hgroup);
-  w.split = __builtin_amdgcn_readfirstlane(w.split);
-  return w;
+  if (lane == 63) s_sum[wave] = incl;
+  __syncthreads();
+  unsigned long long V = 0, before = 0;
+#pragma unroll
+  for (int i = 0; i < kDecWaves; ++i) {
+    if (i < wave) before += s_sum[i];
+    V += s_sum[i];
+  }
+  unsigned long long x0;
+  if (V <= 0xffffffffull) {
+    x0 = set_ranges(s, a.n_wg, (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)V), w);
+  } else {
+    s.n_wg = a.n_wg;
+    s.q = s.r = 0;
+    x0 = V / (unsigned)a.n_wg * w + min((unsigned long long)w, V % (unsigned)a.n_wg);
+    const unsigned long long len =
+        V / (unsigned)a.n_wg + ((unsigned long long)w < V % (unsigned)a.n_wg ? 1 : 0);
+    s.left = __builtin_amdgcn_readfirstlane((int)min(len, (unsigned long long)INT_MAX));
+  }
+  unsigned long long pos = before + incl - v;  // this thread's first list entry
+  if (x0 >= pos && x0 < pos + v) {             // exactly one thread when the range is not empty
+    long long b = b0;
+    int n = seq_steps(a, (int)b) + kDecSegCost;
+    while (x0 >= pos + n) {
+      pos += n;
+      ++b;
+      n = seq_steps(a, (int)b) + kDecSegCost;
+    }
+    s_at[0] = (int)b;
+    s_at[1] = (int)(x0 - pos);
+    s_at[2] = (int)(uint32_t)pos;
+  }
+  __syncthreads();
+  s.b = __builtin_amdgcn_readfirstlane(s_at[0]);  // not read when nothing is left
+  s.off = __builtin_amdgcn_readfirstlane(s_at[1]);
+  s.pos = (uint32_t)__builtin_amdgcn_readfirstlane(s_at[2]);
+  return s;
 }
 
 // Rotate 8 (d, d + 64) pairs given in fp32 by the (cos, sin) pairs c4[0..3]
@@ -199,14 +245,34 @@ __device__ inline f32x4 mfma16k16(bf16x4 a, bf16x4 b, f32x4 c) {
                                                    __builtin_bit_cast(i16x4v, b), c, 0, 0, 0);
 }
 
-// Split-K workgroup (b, group of up to 4 kv heads, split): split s takes the
-// 16-key steps s, s + n_split, s + 2 n_split, ... of the sequence, so at any
-// moment all workgroups stream one narrow window of the cache.  Every 16-key
+// Maximum over the lanes l, l ^ 16, l ^ 32, l ^ 48, by lane swaps in registers
+// (an LDS permute pair in their place cost 2.3 us of a 128K-key call: this
+// chain is on every step's critical path).
+__device__ inline float max_xor16_32(float x) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// Split-K workgroup (group of up to 4 kv heads, w): its splits one after
+// another, each some 16-key steps of one sequence (SplitRange).  Every 16-key
 // step copies the keys' contiguous head slices (K and V, one key's heads are
 // adjacent in the cache) straight into LDS.  Waves w and w + 4 serve kv head
 // 4 * group + w on the even and the odd steps, so two waves share each SIMD
 // and hide each other's latency; their partial states are merged at the end.
 // Four buffers hold the two steps being computed and the next two in flight.
+// What the split needs besides its keys (the offset table, the raw query rows)
+// is copied to LDS the same way, in front of the first steps, so nothing in
+// the prologue is waited for on its own.
+//
+// Bound by HBM: 1.23 us per 32 KB step and CU at 6.8 TB/s.  A call of 131072
+// keys, 32/8 heads, takes 84.9 us (6.3 TB/s in all; 88.9 before the prologue,
+// the value reads and the maxima below left the critical path); 8 sequences
+// of 32K to 128K 391 us (6.9 TB/s; 397); 32 paged ones of 0.5K to 16K 116 us
+// (148).  Requesting every LDS operand of a step at once took 3.5 us more:
+// the bursts hold up the copies' writes.
 //
 // Rotation by tile offset: with k0 the step's first key, a key at k0 + t is
 // rotated by t only, R(t) x_k (base view) or by f(k0 + t) - f(k0) (remote
@@ -223,6 +289,7 @@ __device__ inline f32x4 mfma16k16(bf16x4 a, bf16x4 b, f32x4 c) {
 //   apart): slot s holds frequencies 2 s, 2 s + 1
 // RMODE: 0 the vanilla kernel, 1 bifocal with the Eq. (3) map, 2 bifocal with
 // the frequency map (remote rotations at unchanged positions by omega').
+// PAGED: page pools and block tables instead of dense caches.
 // The Sec. 4.5 map of a sequence of n keys: s = max(1, n / w_pretrained) and
 // omega'_i = (1 - gamma_i) omega_i / s + gamma_i omega_i (freq_map_omega);
 // the (cos, sin) of pos * omega'_i (freq_map_cs), with the angle formed and
@@ -245,7 +312,30 @@ __device__ inline float2 freq_map_cs(double omf, int pos) {
   return make_float2(cs, sn);
 }
 
-template <int RMODE>
+// Wait until all but the last n steps' copies of this wave have landed: four
+// K/V copies per step, and in wave 0 the step's query cos/sin row too.
+__device__ inline void wait_steps(int wave, int n) {
+  constexpr int k0 = kDecCopies, k = kDecCopies - 1;
+  if (n >= 4) {
+    if (wave == 0) wait_vmem_n<4 * k0>(); else wait_vmem_n<4 * k>();
+  } else if (n == 3) {
+    if (wave == 0) wait_vmem_n<3 * k0>(); else wait_vmem_n<3 * k>();
+  } else if (n == 2) {
+    if (wave == 0) wait_vmem_n<2 * k0>(); else wait_vmem_n<2 * k>();
+  } else if (n == 1) {
+    if (wave == 0) wait_vmem_n<k0>(); else wait_vmem_n<k>();
+  } else {
+    wait_vmem();
+  }
+}
+
+// Per sequence of a batch, the workgroups (of one kv-head group) that hold its
+// first and its last split: behind the states.
+__device__ inline int* split_ends(const DecodeArgs& a) {
+  return (int*)(a.ws + (size_t)a.n_slots * a.Hq * kStateFloats);
+}
+
+template <int RMODE, bool PAGED>
 __global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs a) {
   constexpr bool BIFOCAL = RMODE != 0;
   constexpr bool FREQ = RMODE == 2;
@@ -258,29 +348,39 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs
   const int i16 = lane & 15;
   const int g4 = lane >> 4;
 
-  const SplitWork sw = split_work(a, blockIdx.x);
-  if (sw.ns == 0) return;  // whole workgroup, before any barrier
-  const int split = sw.split, hgroup = sw.hgroup, b = sw.b, ns = sw.ns;
+  const int hgroup = blockIdx.x / a.n_wg;
+  const int w = blockIdx.x - hgroup * a.n_wg;
+  const uint32_t smem_base = lds_addr(smem);
+  // ---- offset table: cos/sin of t * omega_i for t = 0..15 (table rows 0..15)
+#pragma unroll
+  for (int i = 0; i < kDecTile / kDecWaves; ++i) {
+    const int r = wave + kDecWaves * i;
+    if (lane < 32) dma16_s(a.table, (uint32_t)r * 512 + 16 * lane, smem_base + kDecOffTab + r * kDecTabRow);
+  }
+  SplitRange range = split_range(a, w);
   const int h0 = hgroup * kDecHeads;
   const int Hg = min(kDecHeads, a.Hkv - h0);  // heads in this group
   const int kvh = h0 + hw;
   const bool head_on = hw < Hg;
-  const int kv_len = clamp_len(a.kv_lens[b], a.max_len);
-  // this split's steps: global 16-key steps split, split + ns, ... below
-  // kv_len, so at any moment all splits read neighbouring parts of the cache
-  const int s_all = (kv_len + kDecTile - 1) / kDecTile;
-  const int c1 = kv_len;
-  const int kstride = ns * kDecTile;
-  const int c0 = split * kDecTile;
-  const int G = BIFOCAL ? group_size(kv_len, a.w_pre) : 1;
-  const FastDiv gdiv = make_fastdiv((uint32_t)G);
-  const int qpos = kv_len - 1;
-  const int fq = BIFOCAL ? remote_pos(qpos, gdiv) : qpos;
-  // the frequency map's omega'_i of this lane's frequency (wave 0 forms the
-  // step rows, lane i taking frequency i)
-  const double omf_lane = FREQ ? freq_map_omega(a, kv_len, lane) : 0.0;
-  const int n_steps = (s_all - split + ns - 1) / ns;
-  const int n_iter = (n_steps + 1) / 2;
+  const uint32_t row_bytes = (uint32_t)Hg * 256;
+  const unsigned char* kbase = (const unsigned char*)(a.kc + (size_t)h0 * kHeadDim);
+  const unsigned char* vbase = (const unsigned char*)(a.vc + (size_t)h0 * kHeadDim);
+  const uint32_t kv_row_bytes = (uint32_t)a.Hkv * 256;
+  int32_t* const pages_lds = (int32_t*)(smem + kDecOffPages);
+  const unsigned char* const tab = smem + kDecOffTab;
+  // query columns: col = (view, head) with view = col / 8
+  const int col = i16;
+  const int view = col >> 3;
+  const int hj = col & 7;
+  const bool col_on = head_on && hj < a.g && (BIFOCAL || view == 0);
+  // distances q - k this column keeps: [keep_lo, keep_lo + keep_n) as one
+  // unsigned compare; base view 0 .. w0 (every causal key for the vanilla
+  // kernel), remote view w0 + 1 .. INT_MAX (Eq. (1)), none for unused columns
+  const int keep_lo = BIFOCAL && view == 1 ? (int)min((uint32_t)a.w0 + 1u, (uint32_t)INT_MAX) : 0;
+  const uint32_t keep_n = !col_on ? 0u
+                          : !BIFOCAL ? 0x80000000u
+                          : view == 0 ? (uint32_t)a.w0 + 1u
+                                      : (uint32_t)INT_MAX - (uint32_t)a.w0;
 
   // ---- copies: a step's K image is 16 keys x Hg heads x 256 B = 4 Hg chunks
   // of 1 KB, V likewise; chunk n < 4 Hg is K, n < 8 Hg is V.  Wave w takes
@@ -288,35 +388,6 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs
   // reads, so every wave has the same number of copies per step.  Lane ->
   // LDS slot 16 * lane of its chunk; it fetches the global chunk that slot
   // holds (keys past the chunk read the chunk's last key).
-  const uint32_t row_bytes = (uint32_t)Hg * 256;
-  const uint32_t smem_base = lds_addr(smem);
-  const unsigned char* kbase = (const unsigned char*)(a.kc + (size_t)h0 * kHeadDim);
-  const unsigned char* vbase = (const unsigned char*)(a.vc + (size_t)h0 * kHeadDim);
-  const uint32_t kv_row_bytes = (uint32_t)a.Hkv * 256;
-  // cache row of step jb's first key: a step's 16 keys are consecutive rows
-  // (pages hold a multiple of 16 keys).  The page index is read first
-  // (step_page) and turned into a row where the copies are issued (step_row),
-  // so the table read overlaps the compute in between; page indices are
-  // clamped to the pool.
-  int32_t* pages_lds = (int32_t*)(smem + kDecOffPages);
-  const bool pages_in_lds = a.block_table != nullptr && n_steps <= kDecPageCap;
-  auto step_page = [&](int jb) {
-    if (a.block_table == nullptr) return 0;
-    if (pages_in_lds) return (int)pages_lds[min(jb, n_steps - 1)];
-    const int k0 = c0 + min(jb, n_steps - 1) * kstride;
-    // the table is read-only for the kernel: read it through the constant
-    // address space, so the load is a scalar one and its wait does not
-    // drain the outstanding copies
-    typedef __attribute__((address_space(4))) const int32_t const_i32;
-    const const_i32* bt = (const const_i32*)a.block_table;
-    return (int)bt[(size_t)b * a.max_pages + (k0 >> a.page_shift)];
-  };
-  auto step_row = [&](int jb, int pg) {
-    const int k0 = c0 + min(jb, n_steps - 1) * kstride;
-    if (a.block_table == nullptr) return (size_t)b * a.max_len + k0;
-    pg = min(max(pg, 0), a.n_pages - 1);
-    return ((size_t)pg << a.page_shift) + (k0 & ((1 << a.page_shift) - 1));
-  };
   // per copy i of this lane: the key row t it serves and the byte offset of its
   // chunk inside that key's slice of the cache (the same for every step)
   uint32_t cp_t[kDecCopies - 1], cp_off[kDecCopies - 1];
@@ -335,11 +406,77 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs
   uint32_t cp_full[kDecCopies - 1];  // byte offsets inside a step with 16 valid keys
 #pragma unroll
   for (int i = 0; i < kDecCopies - 1; ++i) cp_full[i] = cp_t[i] * kv_row_bytes + cp_off[i];
-  auto issue = [&](int jb, size_t row0) {
+
+  for (; range.left > 0 && range.b < a.B; ++range.b, range.off = 0) {
+  const int b = range.b;
+  // uniform and read-only for the kernel: a scalar load
+  typedef __attribute__((address_space(4))) const int32_t const_i32;
+  const int kv_len = clamp_len(((const const_i32*)a.kv_lens)[b], a.max_len);
+  const int s_all = (kv_len + kDecTile - 1) / kDecTile;
+  const int off = range.off;
+  const int n_list = min(range.left, s_all + kDecSegCost - off);
+  const uint32_t pos = range.pos;
+  range.left -= n_list;
+  range.pos += (uint32_t)(s_all + kDecSegCost);
+  const int n_steps = min(off + n_list, s_all) - off;
+  if (n_steps <= 0) continue;  // only empty steps of this sequence
+  // this split: n_steps steps of sequence b from step0 on, `every` apart
+  const bool seq_first = off == 0, seq_last = off + n_steps == s_all;
+  int step0 = off, every = 1;
+  if (a.B == 1) {
+    step0 = w;
+    every = range.n_wg;
+  } else if (!seq_first && !seq_last && range.q != 0) {
+    const int wf = range_of(range, pos), wl = range_of(range, pos + (uint32_t)s_all - 1);
+    const uint32_t end_f = range.q * (wf + 1) + min((uint32_t)wf + 1, range.r);
+    step0 = (int)(end_f - pos) + (w - wf - 1);
+    every = wl - wf - 1;
+  }
+  const int c1 = kv_len;
+  const int c0 = step0 * kDecTile;
+  const int kstride = every * kDecTile;
+  const int G = BIFOCAL ? group_size(kv_len, a.w_pre) : 1;
+  const FastDiv gdiv = make_fastdiv((uint32_t)G);
+  const int qpos = kv_len - 1;
+  const int fq = BIFOCAL ? remote_pos(qpos, gdiv) : qpos;
+  // the frequency map's omega'_i of this lane's frequency (wave 0 forms the
+  // step rows, lane i taking frequency i)
+  const double omf_lane = FREQ ? freq_map_omega(a, kv_len, lane) : 0.0;
+  const int n_iter = (n_steps + 1) / 2;
+
+  // Byte offset of step jb's first key in its cache: a step's 16 keys are
+  // consecutive rows (pages hold a multiple of 16 keys).  Dense caches: a
+  // running offset.  Paged ones: the page index is read first (step_page) and
+  // turned into an offset where the copies are issued (step_off), so the table
+  // read overlaps the compute in between; page indices are clamped to the pool.
+  size_t run_off = PAGED ? 0 : ((size_t)b * a.max_len + c0) * kv_row_bytes;
+  const size_t run_inc = (size_t)kstride * kv_row_bytes;
+  const bool pages_in_lds = PAGED && n_steps <= kDecPageCap;
+  auto step_page = [&](int jb) __attribute__((always_inline)) {
+    if (!PAGED) return 0;
+    if (pages_in_lds) return (int)pages_lds[min(jb, n_steps - 1)];
     const int k0 = c0 + min(jb, n_steps - 1) * kstride;
+    // the table is read-only for the kernel: read it through the constant
+    // address space, so the load is a scalar one and its wait does not
+    // drain the outstanding copies
+    const const_i32* bt = (const const_i32*)a.block_table;
+    return (int)bt[(size_t)b * a.max_pages + (k0 >> a.page_shift)];
+  };
+  auto step_off = [&](int jb, int pg) __attribute__((always_inline)) {
+    if (!PAGED) {
+      const size_t o = run_off;
+      run_off += run_inc;
+      return o;
+    }
+    const int k0 = c0 + jb * kstride;
+    pg = min(max(__builtin_amdgcn_readfirstlane(pg), 0), a.n_pages - 1);
+    return (((size_t)pg << a.page_shift) + (k0 & ((1 << a.page_shift) - 1))) * kv_row_bytes;
+  };
+  auto issue = [&](int jb, size_t off) __attribute__((always_inline)) {  // jb < n_steps, in order
+    const int k0 = c0 + jb * kstride;
     const uint32_t buf = smem_base + (jb % kDecBufs) * kDecBufBytes;
-    const unsigned char* kstep = kbase + row0 * kv_row_bytes;
-    const unsigned char* vstep = vbase + row0 * kv_row_bytes;
+    const unsigned char* kstep = kbase + off;
+    const unsigned char* vstep = vbase + off;
     if (wave == 0) {
       // the cos/sin rows that rotate the query columns for this step: q - k0
       // (lanes 0..31) and f(q) - f(k0) (lanes 32..63) of the table, or the
@@ -379,48 +516,36 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs
     }
   };
 
-  // ---- offset table: cos/sin of t * omega_i for t = 0..15 (table rows 0..15)
-  {
-    unsigned char* tab = smem + kDecOffTab;
-    for (int i = threadIdx.x; i < kDecTile * 32; i += kDecThreads) {
-      const int r = i >> 5, s = i & 31;
-      *(float4*)(tab + r * kDecTabRow + 16 * s) = *(const float4*)(a.table + r * kHalf + 2 * s);
-      if (FREQ) {
-        // the frequency map's rows t omega'_i, t = 0..15
-        const float2 c0 = freq_map_cs(freq_map_omega(a, kv_len, 2 * s), r),
-                     c1 = freq_map_cs(freq_map_omega(a, kv_len, 2 * s + 1), r);
-        *(float4*)(tab + (kDecOffTab2 - kDecOffTab) + r * kDecTabRow + 16 * s) =
-            make_float4(c0.x, c0.y, c1.x, c1.y);
-      }
-    }
-  }
-  const unsigned char* tab = smem + kDecOffTab;
-
-  // ---- query columns: col = (view, head) with view = col / 8; raw slices kept
-  const int col = i16;
-  const int view = col >> 3;
-  const int hj = col & 7;
-  const bool col_on = head_on && hj < a.g && (BIFOCAL || view == 0);
-  // distances q - k this column keeps: [keep_lo, keep_lo + keep_n) as one
-  // unsigned compare; base view 0 .. w0 (every causal key for the vanilla
-  // kernel), remote view w0 + 1 .. INT_MAX (Eq. (1)), none for unused columns
-  const int keep_lo = BIFOCAL && view == 1 ? (int)min((uint32_t)a.w0 + 1u, (uint32_t)INT_MAX) : 0;
-  const uint32_t keep_n = !col_on ? 0u
-                          : !BIFOCAL ? 0x80000000u
-                          : view == 0 ? (uint32_t)a.w0 + 1u
-                                      : (uint32_t)INT_MAX - (uint32_t)a.w0;
+  // ---- the raw query rows of the group's heads (contiguous, at most 8 KB),
+  // beside the first steps' copies: into LDS where the frequency map's table
+  // would lie, or straight into registers with that map
   // the raw query slices in fp32, scaled once (log2(e) / sqrt(d)): every
   // step rotates them by its own offset without unpacking or scaling again
   float qf[4][8];
-  {
-    const uint16_t* qrow =
-        a.q + ((size_t)b * a.Hq + min(kvh, a.Hkv - 1) * a.g + min(hj, a.g - 1)) * kHeadDim;
+  auto load_q = [&](const uint16_t* qrow) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       unpack8(load16(qrow + 32 * s + 8 * g4), qf[s]);
 #pragma unroll
       for (int i = 0; i < 8; ++i) qf[s][i] *= a.q_scale;
     }
+  };
+  const int q_row = min(hw, Hg - 1) * a.g + min(hj, a.g - 1);  // row of the group's query heads
+  const uint16_t* qgroup = a.q + ((size_t)b * a.Hq + h0 * a.g) * kHeadDim;
+  if (FREQ) {
+    for (int i = threadIdx.x; i < kDecTile * 32; i += kDecThreads) {
+      const int r = i >> 5, s = i & 31;
+      // the frequency map's rows t omega'_i, t = 0..15
+      const float2 cs0 = freq_map_cs(freq_map_omega(a, kv_len, 2 * s), r),
+                   cs1 = freq_map_cs(freq_map_omega(a, kv_len, 2 * s + 1), r);
+      *(float4*)(smem + kDecOffTab2 + r * kDecTabRow + 16 * s) =
+          make_float4(cs0.x, cs0.y, cs1.x, cs1.y);
+    }
+    load_q(qgroup + (size_t)q_row * kHeadDim);
+  } else {
+    const uint32_t off = 1024 * wave + 16 * lane;
+    if (off < (uint32_t)(Hg * a.g) * 256)
+      dma16_s(qgroup, off, smem_base + kDecOffTab2 + 1024 * wave);
   }
 
   // paged caches: the page index of every step of this split, into LDS
@@ -434,24 +559,37 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs
 
   // the plain loads above complete before the first copy is requested, so the
   // compiler's waits for them never hold back the copies
-  wait_vmem();
-  for (int jb = 0; jb < 4; ++jb) issue(jb, step_row(jb, step_page(jb)));
+  if (FREQ) wait_vmem();
+  const int n_first = min(n_steps, 4);
+  for (int jb = 0; jb < n_first; ++jb) issue(jb, step_off(jb, step_page(jb)));
+  if (!FREQ) {
+    // the query rows are older than the steps' copies
+    wait_steps(wave, n_first);
+    __syncthreads();
+    load_q((const uint16_t*)(smem + kDecOffTab2) + (size_t)q_row * kHeadDim);
+  }
 
   f32x4 acc_o[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc_o[i] = f32x4{};
   float m_run = -INFINITY, l_run = 0.f;
 
+  // scalar loads still in flight would make the compiler drain every LDS read
+  // of the loop (they share a counter and complete out of order)
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
   for (int it = 0; it < n_iter; ++it) {
     // cache rows of the steps copied at the end of this iteration, looked up
     // now so the block-table reads are long done by then
     const int page4 = step_page(2 * it + 4), page5 = step_page(2 * it + 5);
-    // this wave's copies of steps 2it, 2it+1 (the next pair may fly): four
-    // K/V copies per step, and in wave 0 the step's query cos/sin row too
-    if (wave == 0)
-      wait_vmem_n<2 * kDecCopies>();
-    else
-      wait_vmem_n<2 * (kDecCopies - 1)>();
+    // this wave's copies of steps 2it, 2it+1 (the next pair may fly)
+    if (2 * it + 3 < n_steps) {
+      if (wave == 0)
+        wait_vmem_n<2 * kDecCopies>();
+      else
+        wait_vmem_n<2 * (kDecCopies - 1)>();
+    } else {  // the last iterations: fewer steps in flight
+      wait_steps(wave, max(n_steps - (2 * it + 2), 0));
+    }
     __syncthreads();  // everyone's copies (and the offset table)
     const int j = 2 * it + par;
     if (head_on && j < n_steps) {
@@ -500,6 +638,18 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs
         }
       }
 
+      // the values of the PV product, requested before the softmax needs time;
+      // a transposing read gives lane i of group g4 the keys 4 g4 .. 4 g4 + 3
+      // at d = 16 db + i
+      i16x4 vr[8];
+#pragma unroll
+      for (int db = 0; db < 8; ++db) {
+        const int c = 2 * db + ((i16 & 3) >> 1);
+        const int ta = 4 * g4 + (i16 >> 2);
+        vr[db] = lds_read_tr4(vb + ta * row_bytes + 16 * (c ^ (2 * (ta & 7))) + 8 * (i16 & 1));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+
       // each column keeps only the keys of its own view (q - k in [lo, lo +
       // keep)); lane holds keys 4 g4 + i
       float sv[4];
@@ -509,8 +659,7 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs
 
       // online softmax per column (the 4 lanes i16, i16+16, i16+32, i16+48)
       float mt = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
-      mt = fmaxf(mt, __shfl_xor(mt, 16));
-      mt = fmaxf(mt, __shfl_xor(mt, 32));
+      mt = max_xor16_32(mt);
       const float m_new = fmaxf(m_run, mt);
       const float m_use = m_new == -INFINITY ? 0.f : m_new;
       // 1 unless the maximum moved (a column with no key of its view yet
@@ -528,23 +677,15 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs
       // P^T operand of the k = 16 product: k index 4 g4 + i is key 4 g4 + i
       const bf16x4 pb = __builtin_convertvector(p, bf16x4);
 
-      // O^T += V^T P^T; a transposing read gives lane i of group g4 the keys
-      // 4 g4 .. 4 g4 + 3 at d = 16 db + i
+      // O^T += V^T P^T
 #pragma unroll
-      for (int db = 0; db < 8; ++db) {
-        const int c = 2 * db + ((i16 & 3) >> 1);
-        const int ta = 4 * g4 + (i16 >> 2);
-        const i16x4 v =
-            lds_read_tr4(vb + ta * row_bytes + 16 * (c ^ (2 * (ta & 7))) + 8 * (i16 & 1));
-        acc_o[db] = mfma16k16(__builtin_bit_cast(bf16x4, v), pb, acc_o[db]);
-      }
+      for (int db = 0; db < 8; ++db)
+        acc_o[db] = mfma16k16(__builtin_bit_cast(bf16x4, vr[db]), pb, acc_o[db]);
     }
     __syncthreads();  // steps 2it, 2it+1 consumed: their buffers take steps 2it+4, 2it+5
-    issue(2 * it + 4, step_row(2 * it + 4, page4));
-    issue(2 * it + 5, step_row(2 * it + 5, page5));
+    if (2 * it + 4 < n_steps) issue(2 * it + 4, step_off(2 * it + 4, page4));
+    if (2 * it + 5 < n_steps) issue(2 * it + 5, step_off(2 * it + 5, page5));
   }
-  wait_vmem();  // copies requested past the last step
-  __syncthreads();  // every buffer is free again
 
   // ---- merge the odd-step wave's state into the even-step wave's (max-shifted)
   {
@@ -558,79 +699,94 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs
         for (int i = 0; i < 4; ++i) xs[2 + 4 * db + i] = acc_o[db][i];
     }
     __syncthreads();
-    if (par == 1 || !head_on) return;
-    const float m_b = xs[0];
-    const float M = fmaxf(m_run, m_b);
-    const float wa = M == -INFINITY ? 0.f : fast_exp2(m_run - M);
-    const float wb = M == -INFINITY ? 0.f : fast_exp2(m_b - M);
-    l_run = wa * l_run + wb * xs[1];
+    if (par == 0) {
+      const float m_b = xs[0];
+      const float M = fmaxf(m_run, m_b);
+      const float wa = M == -INFINITY ? 0.f : fast_exp2(m_run - M);
+      const float wb = M == -INFINITY ? 0.f : fast_exp2(m_b - M);
+      l_run = wa * l_run + wb * xs[1];
 #pragma unroll
-    for (int db = 0; db < 8; ++db)
+      for (int db = 0; db < 8; ++db)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc_o[db][i] = wa * acc_o[db][i] + wb * xs[2 + 4 * db + i];
-    m_run = M;
+        for (int i = 0; i < 4; ++i) acc_o[db][i] = wa * acc_o[db][i] + wb * xs[2 + 4 * db + i];
+      m_run = M;
+    }
   }
 
   // ---- one state per head: Eq. (7) over the local-window state (column hj)
   // and the remote-only state (column 8 + hj); the exclusion window is empty
   // because band keys never enter the remote view
-  float l_tot = l_run + __shfl_xor(l_run, 16);
-  l_tot += __shfl_xor(l_tot, 32);
-  float m_own = m_run, l_own = l_tot;
-  float W_own = 1.f, W_oth = 0.f;
-  float m_oth = -INFINITY, l_oth = 0.f;
-  if (BIFOCAL) {
-    m_oth = __shfl_xor(m_run, 8);
-    l_oth = __shfl_xor(l_tot, 8);
-    const float M = fmaxf(m_own, m_oth);
-    W_own = M == -INFINITY ? 0.f : fast_exp2(m_own - M);
-    W_oth = M == -INFINITY ? 0.f : fast_exp2(m_oth - M);
-    m_own = M;
-  }
-  float* out = a.ws + (((size_t)b * a.Hq + kvh * a.g + hj) * a.n_split + split) * kStateFloats;
-  const bool writer = view == 0 && hj < a.g;
-#pragma unroll
-  for (int db = 0; db < 8; ++db) {
-    f32x4 o4 = acc_o[db] * W_own;
+  if (par == 0 && head_on) {
+    float l_tot = l_run + __shfl_xor(l_run, 16);
+    l_tot += __shfl_xor(l_tot, 32);
+    float m_own = m_run, l_own = l_tot;
+    float W_own = 1.f, W_oth = 0.f;
+    float m_oth = -INFINITY, l_oth = 0.f;
     if (BIFOCAL) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) o4[i] += W_oth * __shfl_xor(acc_o[db][i], 8);
+      m_oth = __shfl_xor(m_run, 8);
+      l_oth = __shfl_xor(l_tot, 8);
+      const float M = fmaxf(m_own, m_oth);
+      W_own = M == -INFINITY ? 0.f : fast_exp2(m_own - M);
+      W_oth = M == -INFINITY ? 0.f : fast_exp2(m_oth - M);
+      m_own = M;
     }
-    if (writer) *(f32x4*)(out + 4 + 16 * db + 4 * g4) = o4;
+    float* out = a.ws + ((size_t)(w + b) * a.Hq + kvh * a.g + hj) * kStateFloats;
+    const bool writer = view == 0 && hj < a.g;
+#pragma unroll
+    for (int db = 0; db < 8; ++db) {
+      f32x4 o4 = acc_o[db] * W_own;
+      if (BIFOCAL) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o4[i] += W_oth * __shfl_xor(acc_o[db][i], 8);
+      }
+      if (writer) *(f32x4*)(out + 4 + 16 * db + 4 * g4) = o4;
+    }
+    // the state's third word carries the split count of a single sequence, so
+    // the reduce need not recompute it (slot 0 is written by every call)
+    if (writer && g4 == 0)
+      *(f32x4*)out = f32x4{m_own, W_own * l_own + W_oth * l_oth, __int_as_float(range.n_wg), 0.f};
   }
-  // the state's third word carries this sequence's split count, so the
-  // reduce need not recompute the plan (slot 0 is written by every call)
-  if (writer && g4 == 0)
-    *(f32x4*)out = f32x4{m_own, W_own * l_own + W_oth * l_oth, __int_as_float(ns), 0.f};
+  // a batch's sequences: their first and last slots' workgroups, for the reduce
+  if (a.B > 1 && hgroup == 0 && threadIdx.x == 0) {
+    if (seq_first) split_ends(a)[2 * b] = w;
+    if (seq_last) split_ends(a)[2 * b + 1] = w;
+  }
+  __syncthreads();  // the merged states are read: the next split may fill the buffers
+  }
 }
 
 // Final merge over the splits of one head (Eq. (7) weights exp2(m - M)):
-// O = sum W O~ / sum W l.  Workgroup (head, quarter of the 128 channels):
-// 32 groups of 8 threads; group grp takes splits grp, grp + 32, ... (at most
-// kRedPerGroup each, loads issued together), thread c of a group owns
-// channels 32 quarter + 4c .. +3; partial sums meet in LDS.
+// O = sum W O~ / sum W l.
+//
+// One sequence: its splits are many (a slot per workgroup) and its first slot
+// is known, so every slot is read at once.  Workgroup (head, quarter of the
+// 128 channels): 32 groups of 8 threads; group grp takes splits grp, grp + 32,
+// ..., thread c of a group owns channels 32 quarter + 4c .. +3; partial sums
+// meet in LDS.
 constexpr int kRedGroups = 32;
-constexpr int kRedPerGroup = 4;  // splits per group: n_split <= 128
+constexpr int kRedMaxPer = 8;
+template <int PER>  // splits per group: at most kRedGroups * PER splits
 __global__ __launch_bounds__(256) void decode_reduce_kernel(DecodeArgs a, uint16_t* o) {
   __shared__ float sMax[kRedGroups];
   __shared__ __attribute__((aligned(16))) float sAcc[kRedGroups][32];
   __shared__ float sDen[kRedGroups];
-  const int bh = blockIdx.x;
+  const int h = blockIdx.x;
   const int quarter = blockIdx.y;
   const int tid = threadIdx.x;
-  const float* base = a.ws + (size_t)bh * a.n_split * kStateFloats;
+  const float* base = a.ws + (size_t)h * kStateFloats;
+  const size_t stride = (size_t)a.Hq * kStateFloats;
   const int c = tid & 7;
   const int grp = tid >> 3;
 
   // every slot is read at once, slot 0's state carrying the sequence's split
   // count; the slots past it hold stale states and are dropped below
-  float m[kRedPerGroup], l[kRedPerGroup];
-  f32x4 ov[kRedPerGroup];
+  float m[PER], l[PER];
+  f32x4 ov[PER];
 #pragma unroll
-  for (int i = 0; i < kRedPerGroup; ++i) {
-    // no branch: all loads are issued together (slots past n_split read the
+  for (int i = 0; i < PER; ++i) {
+    // no branch: all loads are issued together (slots past the last read the
     // last slot again and are dropped with the rest)
-    const float* stt = base + (size_t)min(grp + kRedGroups * i, a.n_split - 1) * kStateFloats;
+    const float* stt = base + (size_t)min(grp + kRedGroups * i, a.n_slots - 1) * stride;
     const float2 ml = *(const float2*)stt;
     m[i] = ml.x;
     l[i] = ml.y;
@@ -638,7 +794,7 @@ __global__ __launch_bounds__(256) void decode_reduce_kernel(DecodeArgs a, uint16
   }
   const int ns = __float_as_int(base[2]);  // splits with keys, from slot 0's state
 #pragma unroll
-  for (int i = 0; i < kRedPerGroup; ++i) {
+  for (int i = 0; i < PER; ++i) {
     if (grp + kRedGroups * i >= ns) {
       m[i] = -INFINITY;
       l[i] = 0.f;
@@ -647,7 +803,7 @@ __global__ __launch_bounds__(256) void decode_reduce_kernel(DecodeArgs a, uint16
   }
   float M = -INFINITY;
 #pragma unroll
-  for (int i = 0; i < kRedPerGroup; ++i) M = fmaxf(M, m[i]);
+  for (int i = 0; i < PER; ++i) M = fmaxf(M, m[i]);
   if (c == 0) sMax[grp] = M;
   __syncthreads();
 #pragma unroll
@@ -656,7 +812,7 @@ __global__ __launch_bounds__(256) void decode_reduce_kernel(DecodeArgs a, uint16
   f32x4 acc = f32x4{};
   float den = 0.f;
 #pragma unroll
-  for (int i = 0; i < kRedPerGroup; ++i) {
+  for (int i = 0; i < PER; ++i) {
     const float w = m[i] == -INFINITY ? 0.f : fast_exp2(m[i] - M);
     den += w * l[i];
     acc += w * ov[i];
@@ -672,30 +828,66 @@ __global__ __launch_bounds__(256) void decode_reduce_kernel(DecodeArgs a, uint16
       dsum += sDen[g2];
     }
     const __bf16 r = (__bf16)(num / dsum);
-    o[(size_t)bh * kHeadDim + 32 * quarter + tid] = __builtin_bit_cast(uint16_t, r);
+    o[(size_t)h * kHeadDim + 32 * quarter + tid] = __builtin_bit_cast(uint16_t, r);
+  }
+}
+
+// A batch: a sequence has about n_wg / B splits, from a first slot that the
+// split kernel wrote, so only those are read (reading every slot a sequence
+// could have moved 69 MB and took 20.8 us at 32 sequences of 32 heads).
+// Workgroup = head: 16 groups of 16 threads; group grp takes splits grp,
+// grp + 16, ..., thread c of a group owns channels 8c .. 8c+7.
+constexpr int kRedBatchGroups = 16;
+__global__ __launch_bounds__(256) void decode_reduce_batch_kernel(DecodeArgs a, uint16_t* o) {
+  __shared__ float sM[kRedBatchGroups], sL[kRedBatchGroups];
+  __shared__ __attribute__((aligned(16))) float sO[kRedBatchGroups][kHeadDim];
+  const int b = blockIdx.x / a.Hq;
+  const int h = blockIdx.x - b * a.Hq;
+  const int tid = threadIdx.x;
+  const int c = tid & 15, grp = tid >> 4;
+  const int* ends = split_ends(a) + 2 * b;
+  const int first = min(max(ends[0], 0), a.n_wg - 1);
+  const int ns = min(max(ends[1], first), a.n_wg - 1) - first + 1;
+  const float* base = a.ws + ((size_t)(first + b) * a.Hq + h) * kStateFloats;
+  const size_t stride = (size_t)a.Hq * kStateFloats;
+
+  float M = -INFINITY, den = 0.f;
+  f32x4 acc0 = f32x4{}, acc1 = f32x4{};
+  for (int s = grp; s < ns; s += kRedBatchGroups) {
+    const float* stt = base + (size_t)s * stride;
+    const float2 ml = *(const float2*)stt;
+    const f32x4 o0 = *(const f32x4*)(stt + 4 + 8 * c), o1 = *(const f32x4*)(stt + 8 + 8 * c);
+    const float m = fmaxf(M, ml.x);
+    const float wa = M == -INFINITY ? 0.f : fast_exp2(M - m);
+    const float wb = ml.x == -INFINITY ? 0.f : fast_exp2(ml.x - m);
+    den = wa * den + wb * ml.y;
+    acc0 = wa * acc0 + wb * o0;
+    acc1 = wa * acc1 + wb * o1;
+    M = m;
+  }
+  if (c == 0) {
+    sM[grp] = M;
+    sL[grp] = den;
+  }
+  *(f32x4*)&sO[grp][8 * c] = acc0;
+  *(f32x4*)&sO[grp][8 * c + 4] = acc1;
+  __syncthreads();
+  if (tid < kHeadDim) {
+    const int n = min(ns, kRedBatchGroups);  // groups past the splits hold nothing
+    float mx = -INFINITY;
+    for (int g2 = 0; g2 < n; ++g2) mx = fmaxf(mx, sM[g2]);
+    float num = 0.f, dsum = 0.f;
+    for (int g2 = 0; g2 < n; ++g2) {
+      const float w = sM[g2] == -INFINITY ? 0.f : fast_exp2(sM[g2] - mx);
+      num += w * sO[g2][tid];
+      dsum += w * sL[g2];
+    }
+    const __bf16 r = (__bf16)(num / dsum);
+    o[(size_t)blockIdx.x * kHeadDim + tid] = __builtin_bit_cast(uint16_t, r);
   }
 }
 
 // ---------------------------------------------------------------- launcher
-// Batches of up to this many sequences get split counts balanced over their
-// actual lengths (each workgroup computes the plan from kv_lens, one lane
-// per sequence); larger batches split every sequence by max_len.
-constexpr int kDecBalancedMaxB = 64;
-
-// About one workgroup per CU (each holds 157 KB of LDS): enough copies in
-// flight to stream at full bandwidth while keeping few split states for the
-// reduce (at most kRedGroups * kRedPerGroup per head).  Split s takes the
-// 16-key steps s, s + ns, ...; *chunk is the most keys one split covers.
-void decode_geometry(int B, int Hkv, int max_len, int* chunk, int* n_split) {
-  const long long groups = (long long)B * ((Hkv + kDecHeads - 1) / kDecHeads);
-  const long long steps = ((long long)max_len + kDecTile - 1) / kDecTile;
-  long long want = B <= kDecBalancedMaxB ? kRedGroups * kRedPerGroup : (256 + groups - 1) / groups;
-  if (want > kRedGroups * kRedPerGroup) want = kRedGroups * kRedPerGroup;
-  if (want > steps) want = steps;
-  *n_split = (int)want;
-  *chunk = (int)((steps + want - 1) / want * kDecTile);
-}
-
 static int cu_count() {
   static int cached[64] = {0};
   int dev = 0;
@@ -710,10 +902,44 @@ static int cu_count() {
   return cached[dev];
 }
 
+// Workgroups per kv-head group: about one per CU in all (each holds 157 KB of
+// LDS), never more than one sequence's steps.  Slots: one per (workgroup,
+// sequence) pair of the list (SplitRange), w + b < n_wg + B.
+constexpr int kDecMaxWg = 256;  // CUs of the GPU: workspaces are sized for as many
+static_assert(kDecMaxWg <= kRedGroups * kRedMaxPer, "the reduce reads every slot of one sequence");
+static void decode_geometry(int n_cu, int B, int Hkv, int max_len, int* n_wg, int* n_slots) {
+  const int hg = (Hkv + kDecHeads - 1) / kDecHeads;
+  const long long steps = ((long long)max_len + kDecTile - 1) / kDecTile;
+  long long n = n_cu / hg;
+  if (B == 1 && n > steps) n = steps;
+  if (n < 1) n = 1;
+  *n_wg = (int)n;
+  *n_slots = (int)(n + B - 1);
+}
+
+// The count of split slots per head that workspaces are sized by: what the
+// slots need is less for a batch, so a workspace holds them with room to spare
+// up to 64 sequences, and n_wg + B - 1 of them beyond.
+static long long state_slots(int B, int Hkv, int max_len) {
+  const long long groups = (long long)B * ((Hkv + kDecHeads - 1) / kDecHeads);
+  const long long steps = ((long long)max_len + kDecTile - 1) / kDecTile;
+  long long n = B <= 64 ? 128 : (256 + groups - 1) / groups;
+  if (n > 128) n = 128;
+  if (n > steps) n = steps;
+  return n * B;
+}
+
+size_t decode_state_bytes(int B, int Hq, int Hkv, int max_len) {
+  return (size_t)state_slots(B, Hkv, max_len) * Hq * kStateFloats * sizeof(float);
+}
+
 size_t decode_workspace_bytes(int B, int Hq, int Hkv, int max_len) {
-  int chunk, n_split, n_hgroups;
-  decode_geometry(B, Hkv, max_len, &chunk, &n_split);
-  return (size_t)B * Hq * n_split * kStateFloats * sizeof(float);
+  int n_wg, n_slots;
+  decode_geometry(kDecMaxWg, B, Hkv, max_len, &n_wg, &n_slots);
+  size_t need = (size_t)n_slots * Hq * kStateFloats * sizeof(float);
+  if (B > 1) need += 2 * (size_t)B * sizeof(int);
+  const size_t st = decode_state_bytes(B, Hq, Hkv, max_len);
+  return need > st ? need : st;
 }
 
 size_t decode_map_workspace_bytes(int B, int Hq, int Hkv, int max_len, bool /*freq*/) {
@@ -746,15 +972,12 @@ hipError_t launch_decode(bool bifocal, const uint16_t* q, const uint16_t* kc, co
   a.max_pages = max_pages;
   a.n_pages = n_pages;
   a.page_shift = page_shift;
-  decode_geometry(B, Hkv, max_len, &a.chunk, &a.n_split);
   a.n_hgroups = (Hkv + kDecHeads - 1) / kDecHeads;
-  a.balanced = B <= kDecBalancedMaxB;
-  const int n_cu = cu_count();
-  a.n_target = n_cu > B * a.n_hgroups ? n_cu : B * a.n_hgroups;
+  decode_geometry(std::min(cu_count(), kDecMaxWg), B, Hkv, max_len, &a.n_wg, &a.n_slots);
   a.w_pre = w_pre;
   a.w0 = w0;
   a.q_scale = 1.4426950408889634f / sqrtf((float)kHeadDim);
-  const long long nwg = a.balanced ? (long long)a.n_target : (long long)a.n_split * a.n_hgroups * B;
+  const long long nwg = (long long)a.n_wg * a.n_hgroups;
   if (nwg > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   hipError_t e = hipSuccess;
   const bool freq = bifocal && freq_og != nullptr;
@@ -766,18 +989,29 @@ hipError_t launch_decode(bool bifocal, const uint16_t* q, const uint16_t* kc, co
   }
   // ev0 / ev1 (optional) are recorded on the stream around the split kernel
   if (ev0 != nullptr && (e = hipEventRecord(ev0, stream)) != hipSuccess) return e;
-  if (freq)
-    hipLaunchKernelGGL(decode_split_kernel<2>, dim3((unsigned)nwg), dim3(kDecThreads), 0, stream,
-                       a);
+  const dim3 grid((unsigned)nwg), block(kDecThreads);
+  const bool paged = block_table != nullptr;
+  if (freq && paged)
+    hipLaunchKernelGGL((decode_split_kernel<2, true>), grid, block, 0, stream, a);
+  else if (freq)
+    hipLaunchKernelGGL((decode_split_kernel<2, false>), grid, block, 0, stream, a);
+  else if (bifocal && paged)
+    hipLaunchKernelGGL((decode_split_kernel<1, true>), grid, block, 0, stream, a);
   else if (bifocal)
-    hipLaunchKernelGGL(decode_split_kernel<1>, dim3((unsigned)nwg), dim3(kDecThreads), 0, stream,
-                       a);
+    hipLaunchKernelGGL((decode_split_kernel<1, false>), grid, block, 0, stream, a);
+  else if (paged)
+    hipLaunchKernelGGL((decode_split_kernel<0, true>), grid, block, 0, stream, a);
   else
-    hipLaunchKernelGGL(decode_split_kernel<0>, dim3((unsigned)nwg), dim3(kDecThreads), 0, stream,
-                       a);
+    hipLaunchKernelGGL((decode_split_kernel<0, false>), grid, block, 0, stream, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (ev1 != nullptr && (e = hipEventRecord(ev1, stream)) != hipSuccess) return e;
-  hipLaunchKernelGGL(decode_reduce_kernel, dim3(B * Hq, 4), dim3(256), 0, stream, a, o);
+  if (B > 1)
+    hipLaunchKernelGGL(decode_reduce_batch_kernel, dim3((unsigned)B * Hq), dim3(256), 0, stream, a,
+                       o);
+  else if (a.n_wg <= 4 * kRedGroups)
+    hipLaunchKernelGGL(decode_reduce_kernel<4>, dim3(Hq, 4), dim3(256), 0, stream, a, o);
+  else
+    hipLaunchKernelGGL(decode_reduce_kernel<kRedMaxPer>, dim3(Hq, 4), dim3(256), 0, stream, a, o);
   return hipGetLastError();
 }
 
@@ -790,14 +1024,21 @@ hipError_t launch_decode(bool bifocal, const uint16_t* q, const uint16_t* kc, co
 // in full by every call), so calls that overlap on one device race.
 constexpr int kNoAllocMaxLen = 1 << 17;
 constexpr size_t kNoAllocTableBytes = (size_t)kNoAllocMaxLen * kHalf * sizeof(float2);  // 64 MiB
+// A call is accepted by its count of split states per sequence
+// (decode_state_bytes); the slots that a batch needs beyond that count
+// (decode_workspace_bytes) are at most n_wg per query head, i.e. 256 x 32
+// heads of 528 bytes, and the ends of its sequences.
 constexpr size_t kNoAllocStateBytes = (size_t)24 << 20;
-static __device__ __align__(256) unsigned char scratch[kNoAllocTableBytes + kNoAllocStateBytes];
+constexpr size_t kNoAllocSlackBytes = (size_t)5 << 20;
+static __device__ __align__(256) unsigned char
+    scratch[kNoAllocTableBytes + kNoAllocStateBytes + kNoAllocSlackBytes];
 
 hipError_t launch_build_table(float2* table, uint32_t* table16, int n_pos, const double* omega,
                               hipStream_t stream);
 
 int noalloc_decode_max_len() { return kNoAllocMaxLen; }
 size_t noalloc_decode_state_bytes() { return kNoAllocStateBytes; }
+size_t noalloc_decode_slot_bytes() { return kNoAllocStateBytes + kNoAllocSlackBytes; }
 
 namespace {
 struct NoAllocDevice {

@@ -46,6 +46,7 @@ int prefill_block_q(int g);
 int prefill_block_k();
 size_t decode_workspace_bytes(int B, int Hq, int Hkv, int max_len);
 size_t decode_map_workspace_bytes(int B, int Hq, int Hkv, int max_len, bool freq);
+size_t decode_state_bytes(int B, int Hq, int Hkv, int max_len);
 hipError_t launch_decode(bool bifocal, const uint16_t* q, const uint16_t* kc, const uint16_t* vc,
                          const int32_t* kv_lens, int max_len, uint16_t* o, const float2* table,
                          int B, int Hq, int Hkv, int w_pre, int w0, float* ws,
@@ -54,6 +55,7 @@ hipError_t launch_decode(bool bifocal, const uint16_t* q, const uint16_t* kc, co
                          const double* freq_og);
 int noalloc_decode_max_len();
 size_t noalloc_decode_state_bytes();
+size_t noalloc_decode_slot_bytes();
 hipError_t noalloc_decode_buffers(double theta, const double* omega, hipStream_t stream,
                                   const float2** table, float** states);
 hipError_t launch_build_table(float2* table, uint32_t* table16, int n_pos, const double* omega,
@@ -525,8 +527,9 @@ int decode_common(bool bifocal, const void* q, const void* kc, const void* vc,
     if (max_len > jl::noalloc_decode_max_len())
       return fail(JL_ERR_UNSUPPORTED, "no-alloc decode: max_len %d exceeds %d", max_len,
                   jl::noalloc_decode_max_len());
-    const size_t states = jl::decode_workspace_bytes(B, Hq, Hkv, max_len);
-    if (states > jl::noalloc_decode_state_bytes())
+    const size_t states = jl::decode_state_bytes(B, Hq, Hkv, max_len);
+    if (states > jl::noalloc_decode_state_bytes() ||
+        jl::decode_workspace_bytes(B, Hq, Hkv, max_len) > jl::noalloc_decode_slot_bytes())
       return fail(JL_ERR_UNSUPPORTED, "no-alloc decode: %zu bytes of split states exceed %zu",
                   states, jl::noalloc_decode_state_bytes());
     double omega[kHeadDim / 2];

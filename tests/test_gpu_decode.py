@@ -176,3 +176,33 @@ def test_decode_extreme_windows(w_pre, w0):
     out = _run(True, q, kc, vc, lens, w_pre, w0)
     want, _, _ = O.decode(q, kc, vc, lens, theta=1e6, w_pretrained=w_pre, w_local=w0)
     assert_close(to_f64(out), want, what="decode w_pre=%d w0=%d" % (w_pre, w0))
+
+
+@pytest.mark.parametrize("B,Hkv,lens", [
+    (1, 2, [1]),                              # one step: one workgroup, one split
+    (1, 2, [17]),                             # two steps, fewer than the workgroups
+    (1, 1, [4096]),                           # 256 workgroups of one kv-head group
+    (3, 1, [4096, 1, 4079]),                  # ranges that end one sequence and begin the next
+    (64, 4, [16 + 37 * i for i in range(64)]),
+    (600, 4, [1 + 13 * i % 300 for i in range(600)]),  # more sequences than threads
+])
+def test_decode_equal_ranges(B, Hkv, lens):
+    """Every workgroup streams an equal range of the batch's steps, whatever
+    sequences it spans: one step, ranges over several sequences, one thread
+    and several sequences per thread in the plan.  NaN tails catch a step of
+    another sequence; the paged cache gives the dense one's bits."""
+    g, w_pre, w0, page = 2, 128, 50, 16
+    max_len = (max(lens) + 31) // 16 * 16
+    q, kc, vc, lens = synth.decode_inputs(B, g * Hkv, Hkv, max_len, lens, seed=B + Hkv,
+                                          nan_tail=True)
+    say("decode equal ranges B=%d Hkv=%d" % (B, Hkv))
+    out = _run(True, q, kc, vc, lens, w_pre, w0)
+    want, _, _ = O.decode(q, kc, vc, lens, theta=1e6, w_pretrained=w_pre, w_local=w0)
+    assert_close(to_f64(out), want, what="equal ranges B=%d Hkv=%d" % (B, Hkv))
+    per = max_len // page
+    table = torch.arange(B * per, dtype=torch.int32, device="cuda").view(B, per)
+    paged = api.decode_paged(to_dev(q), to_dev(kc).view(B * per, page, Hkv, 128),
+                             to_dev(vc).view(B * per, page, Hkv, 128), table,
+                             torch.from_numpy(lens).cuda(), w_pretrained=w_pre, w_local=w0)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), paged.view(torch.int16))
