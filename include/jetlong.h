@@ -31,9 +31,9 @@
  *      - the RoPE cos/sin table (per device and rope_theta, grown by
  *        doubling to cover the call's positions): every prefill and decode
  *        entry point; growing allocates and waits for `stream`;
- *      - the prefill scratch (per device and stream): jl_bifocal_prefill,
- *        jl_rope_attention, their _map, _chunk and _varlen forms; growing
- *        waits for `stream`, frees the old buffer and allocates;
+ *      - the packed-prefill scratch (per device and stream): the _varlen
+ *        forms; growing waits for `stream`, frees the old buffer and
+ *        allocates;
  *      - the frequency-map table (one per device): jl_bifocal_prefill_map
  *        with JL_REMOTE_FREQ; a new (rope_theta, L, w_pretrained) waits for
  *        the whole device, then rebuilds the table in place, or in a buffer
@@ -97,11 +97,7 @@ int64_t jl_group_size(int64_t L, int64_t w_pretrained);
  * rotated to the view of the visit (R(k) x_k on the band, R(f(k)) x_k beyond
  * it, Sec. 3.2); the rotated tile is kept only in on-chip memory and no
  * rotated key is written anywhere.
- * Memory: V is transposed into a library-owned scratch buffer of
- * B * Hkv * ceil(L / 64) * 16 KB bytes of tile images plus
- * 4 * B * Hkv * L + 256 bytes for the list of blocks the checked pass reruns,
- * one per (device, stream), grown on demand (growing waits for the stream)
- * and freed by jl_release_caches; q, k, v are only read.
+ * One kernel launch, no scratch; q, k, v are only read.
  */
 int jl_bifocal_prefill(const void* q, const void* k, const void* v, void* o, float* lse, int B,
                        int Hq, int Hkv, int L, int head_dim, double rope_theta, int w_pretrained,
@@ -151,9 +147,7 @@ int jl_bifocal_prefill_map(const void* q, const void* k, const void* v, void* o,
  * ceil(L / w_pretrained)) for every query of the chunk, as in a prefill of
  * length L, so the output equals rows q_start .. L - 1 of
  * jl_bifocal_prefill over the first L cache rows.  The caches are only read:
- * keys are rotated on chip per visit, as in jl_bifocal_prefill, and values
- * [0, L) are transposed into the library scratch, so a chunk costs O(L)
- * extra work on top of its attention.  Requires 0 <= q_start, n_queries >= 1,
+ * keys are rotated on chip per visit, as in jl_bifocal_prefill.  Requires 0 <= q_start, n_queries >= 1,
  * q_start + n_queries <= max_len; other requirements and errors as in
  * jl_bifocal_prefill.
  */
@@ -214,9 +208,8 @@ int jl_rope_attention_chunk_paged(const void* q, const void* k_pages, const void
  * clamped into [0, total_tokens] (a decreasing step gives an empty sequence)
  * and a sequence whose work would not fit the lists sized for well-formed
  * input is skipped; output rows of skipped, cut or uncovered positions are
- * left as they were.  Scratch (the library's, per stream): (Hkv *
- * (ceil(T / 64) + B)) V^T tile images of 16 KB plus two small work lists.  Other
- * requirements and errors as in jl_bifocal_prefill; only the Eq. (3) map.
+ * left as they were.  Scratch (the library's, per stream): a work list of 16
+ * bytes per query block.  Other requirements and errors as in jl_bifocal_prefill; only the Eq. (3) map.
  */
 int jl_bifocal_prefill_varlen(const void* q, const void* k, const void* v, void* o, float* lse,
                               const int32_t* cu_seqlens, int B, int total_tokens, int max_seqlen,
@@ -255,10 +248,9 @@ int jl_rope_attention(const void* q, const void* k, const void* v, void* o, floa
 /*
  * Bytes of device workspace jl_bifocal_prefill_literal needs for this shape:
  * 3 * B * L * Hq * head_dim * 4 (the window outputs) + the window LSEs
- * (3 * B * Hq * L * 4, rounded up to 256) + B * Hkv * ceil(L / 64) * 16 KB
- * (transposed value tiles) + 256 + 4 * B * Hkv * L (the window passes'
- * counters and list of query blocks for the checked rerun).  Returns 0 for
- * invalid arguments.
+ * (3 * B * Hq * L * 4, rounded up to 256) + B * Hkv * ceil(L / 64) * 16 KB +
+ * 256 + 4 * B * Hkv * L (a region that is not used).  Returns 0 for invalid
+ * arguments.
  */
 size_t jl_prefill_literal_workspace_bytes(int B, int Hq, int Hkv, int L, int head_dim);
 
@@ -266,9 +258,8 @@ size_t jl_prefill_literal_workspace_bytes(int B, int Hq, int Hkv, int L, int hea
  * Bifocal prefill with Eq. (7) of Sec. 3.3 taken literally: the three
  * attention calls A (band q - k <= w_local, base rotation), B (all causal
  * keys, remote rotation) and C (band, remote rotation) run as three calls
- * of the attention kernel (each as the fused call runs: a fast pass, then a
- * checked rerun of the blocks it lists), each
- * writing its normalised output O_X and its natural-log LSE_X, and a fourth
+ * of the attention kernel (each as the fused call runs: a fast pass, then the
+ * checked pass of the blocks that need it), each writing its normalised output O_X and its natural-log LSE_X, and a fourth
  * kernel merges them per row with
  *   M = max(LSE_A, LSE_B, LSE_C), W_X = exp(LSE_X - M),
  *   O = (W_A O_A + (W_B O_B - W_C O_C)) / (W_A + (W_B - W_C)),
@@ -285,10 +276,9 @@ size_t jl_prefill_literal_workspace_bytes(int B, int Hq, int Hkv, int L, int hea
  *     (x = 0, 1, 2), O_X as fp32 [B, L, Hq, head_dim] at float offset
  *     x * B * L * Hq * head_dim, and LSE_X as fp32 [B, Hq, L] at float offset
  *     3 * B * L * Hq * head_dim + x * B * Hq * L.
- * When G == 1 the call runs the vanilla kernel, as jl_bifocal_prefill does,
- * with its transposed value tiles in the workspace's tile region; the window
- * outputs and LSEs are left unwritten.  Either way no library scratch is
- * used (only the RoPE table cache, as for every entry point).
+ * When G == 1 the call runs the vanilla kernel, as jl_bifocal_prefill does;
+ * the window outputs and LSEs are left unwritten.  Either way no library
+ * scratch is used (only the RoPE table cache, as for every entry point).
  */
 int jl_bifocal_prefill_literal(const void* q, const void* k, const void* v, void* o, float* lse,
                                int B, int Hq, int Hkv, int L, int head_dim, double rope_theta,
@@ -463,7 +453,8 @@ int jl_debug_prefill_tiles(int L, int Hq, int Hkv, int w_local, int8_t* classes_
  * accumulated; the default is 64, far from anything ordinary data reaches.
  * The fused and vanilla calls first run a pass without that check, which only
  * notes whether a tile's probability sum exceeded 2^log2_bound or a row's
- * total fell below 2^-log2_bound; such blocks are then rerun with the check.
+ * total fell below 2^-log2_bound; such blocks are then run again, by the same
+ * workgroup, with the check.
  * A small bound (e.g. 3) sends almost every block through the rerun and the
  * rescale path, which tests use to check both.  Values outside [1, 100] leave
  * the setting unchanged.  Returns the previous value.  Not for use while
@@ -475,9 +466,9 @@ double jl_debug_prefill_rescale_log2(double log2_bound);
  * Timing hook for benchmarks, process-wide.  which = 0: every later prefill
  * call that runs the fused or vanilla attention kernel (every prefill entry
  * point but the literal one's three window passes) records the HIP event
- * `start` on its stream right before that kernel and `stop` right after its
- * checked rerun, so hipEventElapsedTime(start, stop) is the attention alone
- * (the value-transpose kernel in front of it stays outside).  which = 1: the
+ * `start` on its stream right before that kernel and `stop` right after it,
+ * so hipEventElapsedTime(start, stop) is the attention alone (a packed call's
+ * planning kernels stay outside).  which = 1: the
  * same around the split kernel of every decode call that takes a workspace
  * (all but jl_bifocal_decode_noalloc; the reduce stays outside).
  * start, stop: hipEvent_t created and owned by the caller; NULL, NULL clears

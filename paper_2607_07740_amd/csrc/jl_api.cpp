@@ -18,16 +18,15 @@
 
 namespace jl {
 // kernels (prefill.hip, decode.hip, aux.hip)
-size_t prefill_workspace_bytes(bool bifocal, int B, int Hkv, int L);
 hipError_t launch_prefill_chunk(bool bifocal, const uint16_t* q, const uint16_t* k,
                                 const uint16_t* v, uint16_t* o, float* lse, const float2* table,
                                 const float2* rtable, const uint32_t* table16,
                                 const uint32_t* rtable16, int freq_map, int B, int Hq, int Hkv,
                                 int L, int q_start, int Lq, int kv_stride, int G, int w0,
-                                float slack, void* ws, hipStream_t stream, hipEvent_t ev0,
+                                float slack, hipStream_t stream, hipEvent_t ev0,
                                 hipEvent_t ev1, const int32_t* block_table, int max_pages,
                                 int page_shift, int n_pages);
-size_t prefill_varlen_workspace_bytes(bool bifocal, int B, int T, int Hq, int Hkv, bool freq);
+size_t prefill_varlen_workspace_bytes(int B, int T, int Hq, int Hkv, bool freq);
 hipError_t launch_prefill_varlen(bool bifocal, const uint16_t* q, const uint16_t* k,
                                  const uint16_t* v, uint16_t* o, float* lse, const float2* table,
                                  const uint32_t* table16, const int32_t* cu, int B, int T,
@@ -279,11 +278,10 @@ int get_freq_table(double theta, int L, int w_pre, hipStream_t stream, Tables* o
   return JL_OK;
 }
 
-// ------------------------------------------- prefill scratch, per stream
-// The prefill writes each call's rotated K (one image per view) and
-// transposed V to scratch before its attention kernel reads them.  One buffer
-// per (device, stream): calls on one stream are ordered, so they can share
-// it; a call that needs more waits for its stream before replacing it.
+// ------------------------------------- packed prefill scratch, per stream
+// A packed call's work lists (and frequency-map tables).  One buffer per
+// (device, stream): calls on one stream are ordered, so they can share it; a
+// call that needs more waits for its stream before replacing it.
 struct Scratch {
   int device;
   hipStream_t stream;
@@ -342,9 +340,8 @@ int check_common(int B, int Hq, int Hkv, int head_dim, double theta) {
 }
 
 // literal: run Eq. (7) as three window passes plus a merge, in the caller's
-// workspace (ws, ws_bytes), or at G == 1 the vanilla kernel with its tile
-// images in that workspace's tile region; otherwise the fused or vanilla
-// kernel with the library scratch.
+// workspace (ws, ws_bytes), or at G == 1 the vanilla kernel; otherwise the
+// fused or vanilla kernel.
 int prefill_common(bool bifocal, const void* q, const void* k, const void* v, void* o, float* lse,
                    int B, int Hq, int Hkv, int L, int head_dim, double theta, int w_pre, int w0,
                    void* stream, bool literal = false, void* ws = nullptr, size_t ws_bytes = 0,
@@ -407,23 +404,12 @@ int prefill_common(bool bifocal, const void* q, const void* k, const void* v, vo
       return ok();
     }
   }
-  std::lock_guard<std::mutex> launch_lock(g_prefill_mu);
-  void* scratch = nullptr;
-  if (literal) {
-    // the literal workspace ends with the tile images and rerun list that
-    // the vanilla kernel needs (the same layout as the library scratch)
-    const size_t tail = jl::prefill_workspace_bytes(false, B, Hkv, L);
-    scratch = static_cast<char*>(ws) + (jl::literal_workspace_bytes(B, Hq, Hkv, L) - tail);
-  } else {
-    st = get_scratch(s, jl::prefill_workspace_bytes(use_bifocal, B, Hkv, L), &scratch);
-    if (st != JL_OK) return st;
-  }
   hipEvent_t ev0, ev1;
   timing_events(0, &ev0, &ev1);
   hipError_t e = jl::launch_prefill_chunk(use_bifocal, (const uint16_t*)q, (const uint16_t*)k,
                                           (const uint16_t*)v, (uint16_t*)o, lse, tab.f32, rtab.f32,
                                           tab.f16, rtab.f16, freq_map, B, Hq, Hkv, L, q_start, Lq,
-                                          kv_stride, G, w0, slack, scratch, s, ev0, ev1,
+                                          kv_stride, G, w0, slack, s, ev0, ev1,
                                           block_table, max_pages, page_shift, n_pages);
   if (e != hipSuccess) return hip_fail(e, "prefill launch");
   return ok();
@@ -466,7 +452,7 @@ int prefill_varlen(bool bifocal, const void* q, const void* k, const void* v, vo
   const float slack = (float)g_rescale_log2.load();
   std::lock_guard<std::mutex> launch_lock(g_prefill_mu);
   void* scratch = nullptr;
-  st = get_scratch(s, jl::prefill_varlen_workspace_bytes(bifocal, B, T, Hq, Hkv, freq), &scratch);
+  st = get_scratch(s, jl::prefill_varlen_workspace_bytes(B, T, Hq, Hkv, freq), &scratch);
   if (st != JL_OK) return st;
   double og[128];
   if (freq) freq_map_ramp(theta, w_pre, og);

@@ -6,29 +6,25 @@
 // Prefill is the inclusion-exclusion combination of attention passes over the
 // two views (Sec. 3.3, Eq. (7)), fused into one kernel.
 //
-// Launches per call:
-//  1. vt_prep_kernel transposes V into the byte image of each 64-key tile that
-//     the attention kernel reads in the PV product (a call-scoped buffer; the
-//     caller's K and V are only read).
-//  2. prefill_kernel, a fast pass and then a checked rerun of the blocks the
-//     fast pass listed (see the softmax below), reads raw (pre-RoPE) K tiles from memory straight into
-//     registers, 8 keys per wave, with the cos/sin rows of their positions,
-//     and rotates them to the view of the visit: k_loc = R(k) x_k on band
-//     tiles, k_rem = R(f(k)) x_k on remote tiles (Sec. 3.2, Eqs. (4)-(6): the
-//     cache keeps unrotated keys and the rotation is formed on the fly).  The
-//     rotated tile lives only in LDS, for the QK product of that visit; no
-//     rotated key is ever written to memory.  Each wave rotates its own 8
-//     keys, one rotate-half pair of 16-byte chunks per lane.
+// One launch per call.  prefill_kernel reads raw (pre-RoPE) K tiles from
+// memory straight into registers, 8 keys per wave, with the cos/sin rows of
+// their positions, and rotates them to the view of the visit: k_loc = R(k) x_k
+// on band tiles, k_rem = R(f(k)) x_k on remote tiles (Sec. 3.2, Eqs. (4)-(6):
+// the cache keeps unrotated keys and the rotation is formed on the fly).  The
+// rotated tile lives only in LDS, for the QK product of that visit; no rotated
+// key is ever written to memory.  Each wave rotates its own 8 keys, one
+// rotate-half pair of 16-byte chunks per lane.  V tiles are copied raw to LDS
+// and transposed by the reads of the PV product.
 //
 // Work decomposition: a workgroup is 8 wave64s and owns 256 query rows =
 // (head hl = r / BQ, position q0 + r % BQ) for the g = Hq/Hkv query heads
 // sharing one kv head (GQA packing), BQ = 256 / g.  One workgroup fills a CU
 // (two waves per SIMD at 256 VGPRs each; 64 KB of LDS), and each rotated K
-// tile and V^T image in LDS serves its 256 rows.  A wave owns 32 rows; a
+// tile and V tile in LDS serves its 256 rows.  A wave owns 32 rows; a
 // lane owns one query column of S^T = K Q^T (v_mfma_f32_32x32x16_bf16, lanes l
 // and l + 32 split the column's 16 accumulator rows), and O^T += V^T P^T takes
-// P^T straight from the S^T accumulator registers.  Rotated K tiles and V^T
-// images of 64-key tiles are double-buffered separately.  The loop is
+// P^T straight from the S^T accumulator registers.  Rotated K tiles and V
+// tiles of 64 keys are double-buffered separately.  The loop is
 // software pipelined: while the softmax of tile j runs on the VALU, the QK
 // product of tile j+1 is already on the matrix cores, followed by PV of tile
 // j; meanwhile each wave copies its share of V(j+1) into LDS and rotates its
@@ -41,9 +37,8 @@
 // The common path is exp2, convert and a dot product for the row sum.  A
 // first, fast pass never moves the reference: it only notes, per tile, whether
 // a row's probability sum passed 2^64 and, at the end, whether a row's total
-// fell below 2^-64; a block that trips either writes nothing and is listed.
-// A second launch reruns the listed blocks with the checked kernel, which
-// tests each tile's probability sum after its softmax and, in a rare branch,
+// fell below 2^-64; a block that trips either writes nothing and is run again
+// by the same workgroup with the checked pass, which tests each tile's probability sum after its softmax and, in a rare branch,
 // moves the reference to the tile's largest score (when that lies more than 64
 // above it, or more than 64 below it before anything was accumulated),
 // re-bases the tile and rescales the state.  So every probability stays below
@@ -59,13 +54,12 @@ constexpr int kPfWaves = 8;             // waves per workgroup: two per SIMD
 constexpr int kPfThreads = 64 * kPfWaves;
 constexpr int kPfRows = 32 * kPfWaves;  // query rows per workgroup: 32 per wave
 constexpr int kPfBK = 64;               // keys per tile
-constexpr int kTileBytes = kPfBK * kHeadDim * 2;  // one K tile or one V^T image: 16 KB
-// LDS: rotated K tiles (two buffers) and V^T images (two)
+constexpr int kTileBytes = kPfBK * kHeadDim * 2;  // one K tile or one V tile: 16 KB
+// LDS: rotated K tiles (two buffers) and V tiles (two)
 constexpr int kRotOff = 0, kVtOff = 2 * kTileBytes;
 constexpr int kSmemBytes = 4 * kTileBytes;  // 64 KB
 constexpr int kPfCopyBytes = kTileBytes / kPfWaves;  // each wave's share of a tile copy: 8 keys
 constexpr int kKeysPerWave = kPfBK / kPfWaves;
-constexpr int kRetryCounters = 3;  // rerun counters at the head of the rerun area
 
 // LDS layouts.
 //   rotated K tile: key r (0..63) at r * 256; its 16-byte
@@ -77,104 +71,15 @@ constexpr int kRetryCounters = 3;  // rerun counters at the head of the rerun ar
 //              odd key (the rotation's writes).
 //   (The raw keys and their cos/sin rows go from memory to registers and
 //   never pass through LDS.)
-//   V^T image: d (0..127) at d * 128; slot s of a row holds the 8 keys of
-//              group g = s ^ ((d >> 1) & 7), g = 2 ks + h, in the order
-//              t -> key 16 ks + 8 (t / 4) + 4 h + t % 4 (the k order of the
-//              P^T operand, i.e. of the S^T accumulator rows).  16 lanes
-//              reading 16 consecutive d at one group hit 16 distinct groups.
+//   V tile: key r at r * 256; its 16-byte chunk c sits in slot c ^ 4 (r & 3).
+//              A PV operand (32 d x 16 keys, lane = (d, h), its 8 elements
+//              the keys 16 ks + 8 u + 4 h + 0..3 for u = 0, 1: the k order of
+//              the P^T operand, i.e. of the S^T accumulator rows) is two
+//              transposing reads, u = 0 and 1; each 32-lane half reads 64 B
+//              of 4 consecutive keys, in 4 distinct quarters of the banks.
 __device__ inline int kswz(int r) { return ((r & 15) >> 1) | ((r & 1) << 3); }
 __device__ inline int kimg_off(int r, int c) { return r * 256 + 16 * (c ^ kswz(r)); }
-__device__ inline int vtimg_off(int d, int g) { return d * 128 + 16 * (g ^ ((d >> 1) & 7)); }
-
-struct PrepArgs {
-  const uint16_t* v;
-  uint16_t* vt;  // [B][Hkv][n_tiles] V^T images
-  int B, Hkv, L, n_tiles;  // L: keys [0, L) are valid
-  int kv_stride;           // rows per sequence in v (>= L)
-  // packed variable-length batches: per tile (seq0, L, tile, tile0) with
-  // seq0 the sequence's first row of v and tile0 its first tile; the images
-  // of kv head h sit at (h * n_tiles + tile0 + tile).  nullptr for dense
-  // batches.
-  const int4* twork;
-  int* retry_count;  // zeroed here for the attention kernel that follows
-  // paged caches (nullptr otherwise): v is a pool [n_pages][page][Hkv][128]
-  // and key k of sequence b sits in page block_table[b][k >> page_shift]
-  const int32_t* block_table;
-  int max_pages, page_shift, n_pages;
-};
-
-// Pool row of key k0 (the first key of a tile; pages hold whole tiles) in
-// page `page`, clamped into the pool.
-__device__ inline size_t paged_row(int page, int n_pages, int page_shift, int k0) {
-  page = page < 0 ? 0 : (page >= n_pages ? n_pages - 1 : page);
-  return ((size_t)page << page_shift) + (size_t)(k0 & ((1 << page_shift) - 1));
-}
-
-// One workgroup per (tile, b * Hkv + kvh), or per (tile work item, kvh) for a
-// packed batch.  Keys past the sequence's length are written as zeros.
-__global__ __launch_bounds__(256) void vt_prep_kernel(PrepArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t sv[kPfBK * kHeadDim];
-  // the rerun counters: one per attention pass that follows (the literal
-  // mode's three window passes use three)
-  if (a.retry_count != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kRetryCounters)
-    a.retry_count[threadIdx.x] = 0;
-  int tile, L;
-  size_t seq_row, img;
-  const int kvh_v = blockIdx.y;
-  if (a.twork != nullptr) {
-    const int4 w = a.twork[blockIdx.x];
-    if (w.y <= 0) return;  // no tile here (uniform, before any barrier)
-    tile = w.z;
-    L = w.y;
-    seq_row = (size_t)w.x;
-    img = ((size_t)kvh_v * a.n_tiles + w.w + tile) * (kTileBytes / 2);
-  } else {
-    tile = blockIdx.x;
-    L = a.L;
-    const int b = blockIdx.y / a.Hkv;
-    seq_row = (size_t)b * a.kv_stride;
-    img = ((size_t)blockIdx.y * a.n_tiles + tile) * (kTileBytes / 2);
-  }
-  const int kvh = a.twork != nullptr ? kvh_v : (int)(blockIdx.y % a.Hkv);
-  const int t = threadIdx.x;
-  const int k0 = tile * kPfBK;
-  const size_t row = (size_t)a.Hkv * kHeadDim;
-  // the tile's first key row: paged pools hold whole tiles in a page
-  size_t trow = seq_row + k0;
-  if (a.block_table != nullptr) {
-    const int b = blockIdx.y / a.Hkv;
-    trow = paged_row(a.block_table[(size_t)b * a.max_pages + (k0 >> a.page_shift)], a.n_pages,
-                     a.page_shift, k0);
-  }
-  const uint16_t* vtile = a.v + (trow * a.Hkv + kvh) * kHeadDim;
-
-  // V tile -> LDS, zeros past L
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int idx = t + 256 * i;  // 64 keys x 16 chunks
-    const int r = idx >> 4, c = idx & 15;
-    u32x4 w = u32x4{0, 0, 0, 0};
-    if (k0 + r < L) w = load16(vtile + (size_t)r * row + 8 * c);
-    *(u32x4*)(sv + r * kHeadDim + 8 * c) = w;
-  }
-  __syncthreads();
-
-  // V^T: 128 d x 8 key groups of 16 bytes, 4 per thread
-  unsigned char* vti = (unsigned char*)(a.vt + img);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int p = t + 256 * i;
-    const int d = p >> 3, g = p & 7;
-    const int ks = g >> 1, h = g & 1;
-    uint16_t e[8];
-#pragma unroll
-    for (int tt = 0; tt < 8; ++tt) e[tt] = sv[(16 * ks + 8 * (tt >> 2) + 4 * h + (tt & 3)) * kHeadDim + d];
-    u32x4 w;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) w[q] = (unsigned)e[2 * q] | ((unsigned)e[2 * q + 1] << 16);
-    *(u32x4*)(vti + vtimg_off(d, g)) = w;
-  }
-}
+__device__ inline int vtile_off(int r, int c) { return r * 256 + 16 * (c ^ (4 * (r & 3))); }
 
 struct PrefillArgs {
   const uint16_t* q;
@@ -188,9 +93,9 @@ struct PrefillArgs {
   int rtab_packed;       // packed batch with the frequency map: the remote tables hold
                          // each sequence's own rows, from the sequence's first row on
   const uint16_t* k;     // raw (pre-RoPE) keys, [B][kv_stride][Hkv][128] or packed [T][Hkv][128]
-  const uint16_t* vt;    // V^T tile images from vt_prep_kernel
-  int kv_stride;         // rows per sequence in k (dense batches)
-  int B, Hq, Hkv, L, n_tiles;  // L: keys [0, L), the call's sequence length (G follows it)
+  const uint16_t* v;     // values, laid out as k
+  int kv_stride;         // rows per sequence in k and v (dense batches)
+  int B, Hq, Hkv, L;     // L: keys [0, L), the call's sequence length (G follows it)
   int q_start, Lq;              // query rows: positions q_start .. q_start + Lq - 1 (= L - Lq ..)
   int g, BQ, n_qblocks;
   int w0;         // local window; INT_MAX for the vanilla kernel and window B
@@ -200,16 +105,12 @@ struct PrefillArgs {
                   // was accumulated, below) the reference before it moves (64)
   float* o32;     // window passes: normalised fp32 O_X [B][L][Hq][128]
   // packed variable-length batch (nullptr otherwise): one (seq0, L, q block,
-  // tile0) per Hkv consecutive workgroups; q and o are [T][Hq][128] with
-  // T = Lq, lse is [Hq][T], the sequence's tile images start at tile0 and
-  // each sequence takes its own G = group_size(L, w_pre)
+  // first tile) per Hkv consecutive workgroups; q and o are [T][Hq][128] with
+  // T = Lq, lse is [Hq][T] and each sequence takes its own
+  // G = group_size(L, w_pre)
   const int4* qwork;
   int w_pre;
-  // blocks whose fast pass needs the reference check (see prefill_kernel):
-  // a counter and the workgroup indices; nullptr where unused
-  int* retry_count;
-  int* retry_list;
-  // paged caches (nullptr otherwise): k is a pool [n_pages][page][Hkv][128],
+  // paged caches (nullptr otherwise): k and v are pools [n_pages][page][Hkv][128],
   // pages of at least 64 keys, so a tile lies in one page
   const int32_t* block_table;
   int max_pages, page_shift, n_pages;
@@ -224,8 +125,8 @@ constexpr int kMaxSeqPages = 4096;
 // XCD's L2.  A packed batch reads its work item from the plan instead.
 struct Work {
   int b, kvh, qblk, q_start, q_end, w0, Lk;  // Lk: keys [0, Lk) of the sequence are valid
-  size_t row_base, lse_base, img_base;    // rows of q/o, lse entries, V^T image elements
-  size_t kv_row0;                         // the sequence's first row of k
+  size_t row_base, lse_base;              // rows of q/o, lse entries
+  size_t kv_row0;                         // the sequence's first row of k and v
   size_t rtab_row;                        // the sequence's row 0 in the remote tables
   FastDiv gdiv;
 };
@@ -249,7 +150,6 @@ __device__ inline bool work_of(const PrefillArgs& a, int bid, bool fused, Work& 
     W.q_end = w.y;
     W.row_base = (size_t)w.x;
     W.lse_base = (size_t)w.x;
-    W.img_base = ((size_t)W.kvh * a.n_tiles + w.w) * (kTileBytes / 2);
     W.kv_row0 = (size_t)w.x;
     W.rtab_row = a.rtab_packed ? (size_t)w.x : 0;
     W.Lk = w.y;
@@ -272,7 +172,6 @@ __device__ inline bool work_of(const PrefillArgs& a, int bid, bool fused, Work& 
     W.q_end = a.q_start + a.Lq;  // one past the last query position
     W.row_base = (size_t)b * a.Lq;
     W.lse_base = (size_t)b * a.Hq * a.Lq;
-    W.img_base = (size_t)group * a.n_tiles * (kTileBytes / 2);
     W.kv_row0 = (size_t)b * a.kv_stride;
     W.rtab_row = 0;
     W.Lk = a.L;
@@ -319,14 +218,15 @@ __device__ inline void load_q_operand(const uint16_t* qrow, int half, const floa
 }
 
 
-// SAFE = false (fused and vanilla modes): the fast pass.  It never waits on
-// the softmax reference check; instead it records, without a branch, whether
-// any tile's probability sum exceeded 2^slack, and at the end whether a row's
-// total fell below 2^-slack.  A block with either writes nothing and lists
-// itself; the SAFE launch that follows reruns only the listed blocks with the
-// per-tile check, which moves the reference as needed.  Every mode runs so.
-template <int MODE, bool SAFE, bool PAGED = false>
-__global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
+// One query block.  SAFE = false: the fast pass.  It never waits on the
+// softmax reference check; instead it records, without a branch, whether any
+// tile's probability sum exceeded 2^slack, and at the end whether a row's
+// total fell below 2^-slack.  A block with either writes nothing and returns
+// true; the kernel then runs it again with SAFE = true: the per-tile check,
+// which moves the reference as needed.  Every mode runs so.
+template <int MODE, bool SAFE, bool PAGED>
+__device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& W,
+                                              unsigned char* smem, int* s_bad, int* s_pages) {
   constexpr bool CHECK_LATE = !SAFE;
   // The visit list has at most two segments: the fused kernel's remote tiles
   // (segment 1), then tiles [kt_l, n_kt) in one view, keeping 0 <= q - k <= w0
@@ -335,25 +235,14 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
   constexpr bool REMOTE2 = MODE == kModeWinB || MODE == kModeWinC;  // segment 2's view
   constexpr bool OUT_F32 = MODE == kModeWinA || MODE == kModeWinB || MODE == kModeWinC;
   constexpr bool FROM_ZERO = MODE == kModeVanilla || MODE == kModeWinB;  // kt_l = 0
-  // LDS: raw K tiles, rotated K tiles and V^T images, two buffers each
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kSmemBytes];
-  __shared__ int s_bad;
-  __shared__ int s_pages[PAGED ? kMaxSeqPages : 1];  // paged caches: the sequence's pages
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
   const int hl32 = lane >> 5;  // which 8-wide half of a 16-wide k slice this lane feeds
 
-  int bid = blockIdx.x;
-  if (SAFE && a.retry_list != nullptr) {  // rerun of the listed blocks only
-    if (bid >= *a.retry_count) return;    // uniform, before any barrier
-    bid = a.retry_list[bid];
-  }
-  Work W;
-  if (!work_of(a, bid, FUSED, W)) return;  // uniform, before any barrier
   const int kvh = W.kvh, qblk = W.qblk, q_start = W.q_start, q_end = W.q_end, w0 = W.w0, Lk = W.Lk;
-  const size_t row_base = W.row_base, lse_base = W.lse_base, img_base = W.img_base;
+  const size_t row_base = W.row_base, lse_base = W.lse_base;
   const size_t kv_row0 = W.kv_row0;
   const float2* rtable = a.rtable + W.rtab_row * kHalf;
   const uint32_t* rtable16 = a.rtable16 + W.rtab_row * kHalf;
@@ -378,11 +267,10 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
   const int kt_l = FROM_ZERO ? 0 : vr.kt_l;
   const int n_steps = n_r + (n_kt - kt_l);
 
-  // ---- staging.  For list entry j each wave copies its eighth (2 KB) of the
-  // V^T image into buffer jb & 1, and rotates 8 keys of the raw K tile, read
+  // ---- staging.  For list entry j each wave copies its 8 keys of the V tile
+  // into buffer jb & 1, and rotates the same 8 keys of the raw K tile, read
   // from memory, into the rotated buffer of that parity.
   const uint32_t smem_base = lds_addr(smem);
-  const uint32_t lane_off = 16 * lane;
   auto tile_of = [&](int j) __attribute__((always_inline)) { return j < n_r ? j : kt_l + (j - n_r); };
   // j's view: remote (R(f(k)), Eq. (3), or the frequency map's table at k) or base (R(k))
   auto is_remote = [&](int j) __attribute__((always_inline)) { return REMOTE2 || (FUSED && j < n_r); };
@@ -399,6 +287,16 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
     int row0, tlim;  // first cos/sin row; index of the last valid row
     int kmod;
     int alias, remote;
+    size_t off;      // the first key's element offset in k and v
+  };
+  // the tile's first row of k and v (paged: its page; a page holds whole tiles)
+  auto tile_row = [&](int k0) __attribute__((always_inline)) {
+    if constexpr (PAGED) {
+      const int page = __builtin_amdgcn_readfirstlane(s_pages[k0 >> a.page_shift]);
+      return ((size_t)page << a.page_shift) + (k0 & ((1 << a.page_shift) - 1));
+    } else {
+      return kv_row0 + k0;
+    }
   };
   const uint32_t G_d = gdiv.d;
   auto ent_of = [&](int j) __attribute__((always_inline)) {
@@ -415,15 +313,20 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
     e.row0 = e.alias ? (int)f0 : e.k0;
     e.kmod = e.alias ? (int)km : 0;
     e.tlim = e.alias ? (int)fl : nlast;
+    e.off = (tile_row(e.k0) * a.Hkv + kvh) * kHeadDim;
     return e;
   };
-  const size_t kseq_off = (kv_row0 * a.Hkv + kvh) * kHeadDim;  // the sequence's key 0 in k
-  auto issue_v = [&](int j, int jb) __attribute__((always_inline)) {
-    const size_t off = img_base + (size_t)tile_of(j) * (kTileBytes / 2) + wave * (kPfCopyBytes / 2);
-    const unsigned char* gv = (const unsigned char*)(a.vt + off);
+  // V(j): copy i takes keys 8 wave + 4 i .. + 3 of the tile, lane -> key
+  // lane / 16 of them and slot lane % 16, i.e. the chunk that slot holds.
+  // Rows past the sequence repeat its last key: their probabilities are zero.
+  const int vrow = 8 * wave + (lane >> 4);
+  const uint32_t vchunk = 16 * ((lane & 15) ^ (4 * (lane >> 4)));
+  const uint32_t kv_row_bytes = (uint32_t)a.Hkv * (kHeadDim * 2);  // < 2^24
+  auto issue_v = [&](const Ent& e, int jb) __attribute__((always_inline)) {
+    const unsigned char* gv = (const unsigned char*)(a.v + e.off);
     const uint32_t l = smem_base + kVtOff + (jb & 1) * kTileBytes + wave * kPfCopyBytes;
-    dma16_s<0>(gv, lane_off, l);
-    dma16_s<1024>(gv, lane_off, l);
+    dma16_s<0>(gv, __umul24((uint32_t)min(vrow, e.klim), kv_row_bytes) + vchunk, l);
+    dma16_s<0>(gv, __umul24((uint32_t)min(vrow + 4, e.klim), kv_row_bytes) + vchunk, l + 1024);
   };
   // Rotation of an entry's raw K tile to its view (Sec. 3.2): lane -> key
   // rt_row of the tile, rotate-half pairs of chunks (rt_c, rt_c + 8), i.e.
@@ -445,14 +348,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
     asm volatile("" : "+v"(fr));  // formed unconditionally: a select, not a branch
     const int row = min(e.alias ? fr : rt_row, e.tlim);
     const int key = min(rt_row, e.klim);
-    const uint16_t* kr;
-    if constexpr (PAGED) {  // the tile's page (clamped already; a page holds whole tiles)
-      const int page = __builtin_amdgcn_readfirstlane(s_pages[e.k0 >> a.page_shift]);
-      const size_t prow = ((size_t)page << a.page_shift) + (e.k0 & ((1 << a.page_shift) - 1));
-      kr = a.k + ((prow + key) * a.Hkv + kvh) * kHeadDim;
-    } else {
-      kr = a.k + kseq_off + (size_t)(e.k0 + key) * ((size_t)a.Hkv * kHeadDim);
-    }
+    const uint16_t* kr =
+        (const uint16_t*)((const unsigned char*)(a.k + e.off) + __umul24((uint32_t)key, kv_row_bytes));
     const uint32_t* tr =
         (e.remote ? rtable16 : a.table16) + (size_t)(e.row0 + row) * kHalf + 8 * rt_c;
     RotIn r;
@@ -522,13 +419,19 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
       if (m + 4 < 16) ring[m & 3] = kop(m + 4);
     }
   };
+  // V^T operand of PV step m (keys 16 (m / 4) .., d 32 (m % 4) ..): lane ->
+  // key vk_lane of each 8-key half and 4 d's of it, transposed by the read
+  const int vk_lane = 4 * hl32 + ((lane & 15) >> 2);
+  const int vc_lane = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+  auto v_operand = [&](const unsigned char* vb, int m) __attribute__((always_inline)) {
+    const unsigned char* p = vb + 4096 * (m >> 2) + vtile_off(vk_lane, 4 * (m & 3) + vc_lane) +
+                             8 * (lane & 1);
+    return concat_tr(lds_read_tr4(p), lds_read_tr4(p + 2048));
+  };
   // O^T += V^T P^T: 4 k-steps of 16 keys x 4 d-blocks of 32, V^T operands
   // read 4 MFMAs ahead
   auto pv = [&](const unsigned char* vb, const bf16x8* pb) __attribute__((always_inline)) {
-    auto vop = [&](int m) __attribute__((always_inline)) {
-      const int d = 32 * (m & 3) + kr_lane;
-      return *(const bf16x8*)(vb + vtimg_off(d, 2 * (m >> 2) + hl32));
-    };
+    auto vop = [&](int m) __attribute__((always_inline)) { return v_operand(vb, m); };
     bf16x8 ring[4];
 #pragma unroll
     for (int m = 0; m < 4; ++m) ring[m] = vop(m);
@@ -644,37 +547,30 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
   };
 
   // One pipelined visit: on entry `cur` holds the scores of tile j, the
-  // rotated K of list entry j+1 is in LDS, and this wave's copies of raw
-  // K(j+2) (with its cos/sin rows) and V(j) are in flight.  The QK product of
-  // entry j+1 is issued next to the softmax of tile j, then PV of tile j; raw
-  // K(j+3) and V(j+1) are copied meanwhile and raw K(j+2) is rotated.  For the last tile of a
-  // segment the QK product reads whatever the next K buffer holds and is
-  // discarded.
-  // pend describes entry j+2 (formed when its copies were issued); on return
-  // it describes entry j+3.
-  auto visit = [&](int j, f32x16* cur, f32x16* nxt, int lo, int hi, Ent& pend) __attribute__((always_inline)) {
+  // rotated K of list entry j+1 is in LDS, and this wave's copy of V(j) is in
+  // flight.  The QK product of entry j+1 is formed next to the softmax of
+  // tile j, then PV of tile j; V(j+1) is copied meanwhile, and raw K(j+2) is
+  // loaded and rotated.  For the last tile of a segment the QK product reads
+  // whatever the next K buffer holds and is discarded.
+  // vent describes entry j+1 and pend entry j+2; on return they are one on.
+  auto visit = [&](int j, f32x16* cur, f32x16* nxt, int lo, int hi, Ent& vent, Ent& pend) __attribute__((always_inline)) {
     if (SAFE ? need_mask(j) : (j < lo || j > hi)) mask(j, cur);
     wait_vmem();      // this wave's copy of V(j)
     __syncthreads();  // everyone's; QK(j), PV(j-1) and the rotation of j+1 are done everywhere
     bf16x8 pb[4];
-    // V(j+1) into the buffer PV(j-1) released
-    issue_v(min(j + 1, n_steps - 1), j + 1);
     if constexpr (!SAFE) {
-      // raw K(j+2) and its cos/sin row into registers: they land while
-      // QK(j+1) and the softmax of j run
-      const RotIn rin = rot_load(pend);
-      // The visit is written as two streams cut by scheduling barriers: each
-      // MFMA of the QK product of j+1 with its operand read and one
-      // sixteenth of the softmax of j (two probabilities, and the bf16 pair
-      // of the previous sixteenth); each MFMA of the PV product of j with its
-      // operand read, one bf16 pair's dot product for the row sum and, on
-      // four of them, a quarter of the rotation of j+2.  The barriers keep
-      // the operand reads and the rotation quarters in place.  The pure
-      // arithmetic is placed before them, by instruction selection: the
-      // exp2 and conversions come together after the QK product's MFMAs and
-      // the row-sum dot products after the PV product.  Forcing the written
-      // interleave with empty asm ties on each result measured 3% slower on
-      // gfx950, and so did leaving the rotation to the compiler as well.
+      // The visit runs in blocks: the QK product of j+1 (each MFMA with an
+      // operand read, cut by scheduling barriers), the softmax of j, the PV
+      // product of j, then the rotation of j+2 and the row sums.  The two
+      // waves of a SIMD pass the blocks together.  Exponentials among the QK
+      // MFMAs instead of behind them gained nothing (the stream is already as
+      // long as its operand reads), and dot products among MFMAs cost far
+      // more than behind them, since the two do not overlap: the rotation
+      // between the PV MFMAs cost 1.5% (4% on zero inputs, where the clock
+      // does not give way), the row sums there 5%.  At 40001 positions (32/8
+      // heads, G = 2) this order takes 11.07 ms, and 8.76 on zero inputs
+      // (11.45 and 9.53 with the rotation in the PV stream, the loads in front
+      // of the QK stream and V transposed by a kernel of its own).
       const unsigned char* kb = kbuf(j + 1);
       auto kop = [&](int m) __attribute__((always_inline)) {
         const int r = 32 * (m & 1) + kr_lane;
@@ -683,22 +579,34 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
       bf16x8 ring[4];
 #pragma unroll
       for (int m = 0; m < 4; ++m) ring[m] = kop(m);
-      bf16x2 pw[16];
-      float e0 = 0.f, e1 = 0.f;
+      __builtin_amdgcn_sched_barrier(0);
+      RotIn rin;
 #pragma unroll
       for (int m = 0; m < 16; ++m) {
         const int blk = m & 1, st = m >> 1;
         nxt[blk] = mfma32(ring[m & 3], qop[st], st == 0 ? neg_m : nxt[blk]);
         if (m + 4 < 16) ring[m & 3] = kop(m + 4);
+        __builtin_amdgcn_sched_barrier(0);
+        if (m == 5) {
+          // V(j+1) into the buffer PV(j-1) released, and raw K(j+2) with its
+          // cos/sin row into registers.  The address arithmetic runs in the
+          // shadow of this stream's MFMAs, and the loads land while the rest
+          // of it, the softmax and the PV product of j run.  In front of the
+          // stream, where the matrix cores wait for it, it cost 1.9%; behind
+          // MFMA 1 0.8%, behind MFMA 9 1.3%.
+          issue_v(vent, j + 1);
+          rin = rot_load(pend);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      bf16x2 pw[16];
+#pragma unroll
+      for (int m = 0; m < 16; ++m) {
         const int q = m >> 2, t = 2 * (m & 3);
         const float p0 = fast_exp2(cur[q >> 1][8 * (q & 1) + t]);
         const float p1 = fast_exp2(cur[q >> 1][8 * (q & 1) + t + 1]);
-        if (m > 0) pw[m - 1] = __builtin_convertvector((f32x2){e0, e1}, bf16x2);
-        e0 = p0;
-        e1 = p1;
-        __builtin_amdgcn_sched_barrier(0);
+        pw[m] = __builtin_convertvector((f32x2){p0, p1}, bf16x2);
       }
-      pw[15] = __builtin_convertvector((f32x2){e0, e1}, bf16x2);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         pb[q] = (bf16x8){pw[4 * q][0], pw[4 * q][1], pw[4 * q + 1][0], pw[4 * q + 1][1],
@@ -706,33 +614,32 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
       // past the list's end the last entry is rotated (and V copied) again
       const Ent e3 = ent_of(min(j + 3, n_steps - 1));
       const unsigned char* vb = vbuf(j);
-      auto vop = [&](int m) __attribute__((always_inline)) {
-        const int d = 32 * (m & 3) + kr_lane;
-        return *(const bf16x8*)(vb + vtimg_off(d, 2 * (m >> 2) + hl32));
-      };
+      auto vop = [&](int m) __attribute__((always_inline)) { return v_operand(vb, m); };
 #pragma unroll
       for (int m = 0; m < 4; ++m) ring[m] = vop(m);
-      // the rotated words in units 1, 4, 7, 10; stored early, so the writes
-      // are done well before the next barrier
-      u32x4 rlo, rhi;
-      float ps0 = 0.f, ps1 = 0.f;
 #pragma unroll
       for (int m = 0; m < 16; ++m) {
         acc_o[m & 3] = mfma32(ring[m & 3], pb[m >> 2], acc_o[m & 3]);
         if (m + 4 < 16) ring[m & 3] = vop(m + 4);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      rotate(rin, j + 2);  // into the buffer QK(j) released
+      __builtin_amdgcn_sched_barrier(0);  // its LDS writes go out ahead of the next barrier
+      float ps0 = 0.f, ps1 = 0.f;
+#pragma unroll
+      for (int m = 0; m < 16; ++m) {
         if (m & 1)
           ps1 = __builtin_amdgcn_fdot2_f32_bf16(pw[m], bf16_one2(), ps1, false);
         else
           ps0 = __builtin_amdgcn_fdot2_f32_bf16(pw[m], bf16_one2(), ps0, false);
-        if (m % 3 == 1 && m < 12) rot_word(rin, m / 3, rlo, rhi);
-        if (m == 11) rot_store(j + 2, rlo, rhi);  // into the buffer QK(j) released
-        __builtin_amdgcn_sched_barrier(0);
       }
       const float ps = ps0 + ps1;
       late_bad |= __ballot(ps > p_hi);
       l_run += ps;
+      vent = pend;
       pend = e3;
     } else {
+      issue_v(vent, j + 1);  // into the buffer PV(j-1) released
       __builtin_amdgcn_iglp_opt(0);
       qk(kbuf(j + 1), nxt);
       const Ent e3 = ent_of(min(j + 3, n_steps - 1));
@@ -742,16 +649,17 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
       const RotIn rin = rot_load(pend);  // loaded late: short-lived registers
       pv(vbuf(j), pb);
       rotate(rin, j + 2);
+      vent = pend;
       pend = e3;
     }
   };
   // segment [j, jend): the first tile's scores are in sc_a on entry
-  auto segment = [&](int j, int jend, int lo, int hi, Ent& pend) __attribute__((always_inline)) {
+  auto segment = [&](int j, int jend, int lo, int hi, Ent& vent, Ent& pend) __attribute__((always_inline)) {
     for (; j + 2 <= jend; j += 2) {
-      visit(j, sc_a, sc_b, lo, hi, pend);
-      visit(j + 1, sc_b, sc_a, lo, hi, pend);
+      visit(j, sc_a, sc_b, lo, hi, vent, pend);
+      visit(j + 1, sc_b, sc_a, lo, hi, vent, pend);
     }
-    if (j < jend) visit(j, sc_a, sc_b, lo, hi, pend);
+    if (j < jend) visit(j, sc_a, sc_b, lo, hi, vent, pend);
   };
 
   // ---- prologue: the first view's query operand; K(0), K(1) rotated into
@@ -759,7 +667,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
   const bool q_remote = n_r > 0 || REMOTE2;
   load_q_operand(qrow, hl32, q_remote ? rtable : a.table,
                  q_remote && !a.freq_map ? remote_pos(qp, gdiv) : qp, a.q_scale, qop);
-  if (CHECK_LATE && tid == 0) s_bad = 0;  // read after the end-of-block barrier
+  if (CHECK_LATE && tid == 0) *s_bad = 0;  // read after the end-of-block barrier
   const int last = n_steps - 1;
   if constexpr (PAGED) {  // the sequence's page list, clamped into the pool
     const int np = min((Lk + (1 << a.page_shift) - 1) >> a.page_shift, kMaxSeqPages);
@@ -769,11 +677,10 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
     }
     __syncthreads();
   }
-  Ent pend = ent_of(0);
+  Ent pend = ent_of(0), vent = ent_of(min(1, last));
   {
-    const Ent e1 = ent_of(min(1, last));
-    issue_v(0, 0);
-    const RotIn r0 = rot_load(pend), r1 = rot_load(e1);
+    issue_v(pend, 0);
+    const RotIn r0 = rot_load(pend), r1 = rot_load(vent);
     rotate(r0, 0);
     rotate(r1, 1);
   }
@@ -784,7 +691,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
   if (FUSED && n_r > 0) {
     int lo = 0, hi = 0;
     if (!SAFE) seg1_bounds(lo, hi);
-    segment(0, n_r, lo, hi, pend);
+    segment(0, n_r, lo, hi, vent, pend);
     // segment 2 in the base view: its first tile, already rotated to the base
     // view (buffer n_r & 1, not overwritten since), is scored again with the
     // base-rotated query operand
@@ -794,7 +701,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
   {
     int lo = 0, hi = 0;
     if (!SAFE) seg2_bounds(lo, hi);
-    segment(n_r, n_steps, lo, hi, pend);
+    segment(n_r, n_steps, lo, hi, vent, pend);
   }
   wait_vmem();  // the copies past the list's end
 
@@ -802,12 +709,9 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   if (CHECK_LATE) {
     late_bad |= __ballot(row_valid && !(l_tot >= p_lo));
-    if (late_bad != 0 && lane == 0) s_bad = 1;
+    if (late_bad != 0 && lane == 0) *s_bad = 1;
     __syncthreads();
-    if (s_bad != 0) {
-      if (tid == 0) a.retry_list[atomicAdd(a.retry_count, 1)] = bid;
-      return;
-    }
+    if (__builtin_amdgcn_readfirstlane(*s_bad) != 0) return true;
   }
   if (row_valid) {
     const float inv = 1.f / l_tot;
@@ -828,6 +732,21 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
     }
     if (a.lse != nullptr && hl32 == 0)
       a.lse[lse_base + (size_t)hd * a.Lq + qr] = (m_ref + log2f(l_tot)) * 0.69314718055994531f;
+  }
+  return false;
+}
+
+template <int MODE, bool PAGED = false>
+__global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
+  // LDS: rotated K tiles and V tiles, two buffers each
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kSmemBytes];
+  __shared__ int s_bad;
+  __shared__ int s_pages[PAGED ? kMaxSeqPages : 1];  // paged caches: the sequence's pages
+  Work W;
+  if (!work_of(a, blockIdx.x, MODE == kModeFused, W)) return;  // uniform, before any barrier
+  if (prefill_block<MODE, false, PAGED>(a, W, smem, &s_bad, s_pages)) {
+    __syncthreads();  // every wave is done with the fast pass's tiles
+    prefill_block<MODE, true, PAGED>(a, W, smem, &s_bad, s_pages);
   }
 }
 
@@ -874,81 +793,43 @@ __global__ __launch_bounds__(256) void literal_merge_kernel(MergeArgs a) {
 }
 
 // ---------------------------------------------------------------- launchers
-// V^T tile images, then the retry counter (256 B) and list (one int per
-// workgroup: at most L query blocks per (b, kv head), since BQ = rows / g can
-// be as small as 1).  No rotated key is ever stored: K is read raw by the
-// attention kernel.
-static size_t retry_bytes(long long nwg) { return 256 + (size_t)nwg * sizeof(int); }
-
-static size_t image_bytes(int B, int Hkv, int L) {
-  const size_t tiles = (size_t)(L + kPfBK - 1) / kPfBK;
-  return (size_t)B * Hkv * tiles * kTileBytes;
-}
-
-size_t prefill_workspace_bytes(bool /*bifocal*/, int B, int Hkv, int L) {
-  return image_bytes(B, Hkv, L) + retry_bytes((long long)B * Hkv * L);
-}
-
 // Literal mode workspace: O_A, O_B, O_C (fp32 [B][L][Hq][128] each), then
 // LSE_A, LSE_B, LSE_C (fp32 [B][Hq][L] each), then at the next 256-byte
-// boundary the V^T images and the window passes' rerun counters and list,
-// laid out as the library scratch.
+// boundary a region of 16 KB per key tile and kv head and 4 bytes per key and
+// kv head that the size has always included; nothing uses it.
 static size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 size_t literal_workspace_bytes(int B, int Hq, int Hkv, int L) {
   const size_t rows = (size_t)B * L * Hq;
+  const size_t tiles = (size_t)(L + kPfBK - 1) / kPfBK;
   return 3 * rows * kHeadDim * sizeof(float) + round256(3 * rows * sizeof(float)) +
-         image_bytes(B, Hkv, L) + retry_bytes((long long)B * Hkv * L);
+         (size_t)B * Hkv * tiles * kTileBytes + 256 + (size_t)B * Hkv * L * sizeof(int);
 }
 
-// rtable: the remote view's table, nullptr for the aliasing map (then the
-// base table is read at f(p)); with freq_map it is read at p.  With
-// `retry`, the rerun counter and list follow the images (the prep kernel
-// zeroes the counter); without, nothing past the images is touched.
 struct Paging {
   const int32_t* block_table;  // nullptr: dense caches
   int max_pages, page_shift, n_pages;
 };
 
-static hipError_t launch_prep(const uint16_t* k, const uint16_t* v, const float2* table,
-                              const float2* rtable, const uint32_t* table16,
-                              const uint32_t* rtable16, int freq_map, int B, int Hkv, int L,
-                              int kv_stride, int G, void* images, bool retry, PrefillArgs& a,
-                              hipStream_t stream, Paging pg = Paging{nullptr, 0, 0, 0}) {
+// rtable: the remote view's table, nullptr for the aliasing map (then the
+// base table is read at f(p)); with freq_map it is read at p.
+static void fill_inputs(PrefillArgs& a, const uint16_t* q, const uint16_t* k, const uint16_t* v,
+                        const float2* table, const float2* rtable, const uint32_t* table16,
+                        const uint32_t* rtable16, int freq_map, int kv_stride, int G,
+                        Paging pg = Paging{nullptr, 0, 0, 0}) {
+  a.q = q;
+  a.k = k;
+  a.v = v;
+  a.kv_stride = kv_stride;
   a.block_table = pg.block_table;
   a.max_pages = pg.max_pages;
   a.page_shift = pg.page_shift;
   a.n_pages = pg.n_pages;
-  const int n_tiles = (L + kPfBK - 1) / kPfBK;
-  const size_t img = (size_t)B * Hkv * n_tiles * (kTileBytes / 2);  // bf16 elements of the images
-  a.k = k;
-  a.kv_stride = kv_stride;
-  a.vt = (const uint16_t*)images;
-  a.retry_count = retry ? (int*)(a.vt + img) : nullptr;
-  a.retry_list = retry ? a.retry_count + 64 : nullptr;
-  a.n_tiles = n_tiles;
   a.table = table;
   a.rtable = freq_map ? rtable : table;
   a.table16 = table16;
   a.rtable16 = freq_map ? rtable16 : table16;
   a.freq_map = freq_map;
   a.gdiv = make_fastdiv((uint32_t)G);
-
-  PrepArgs p = {};
-  p.v = v;
-  p.vt = (uint16_t*)a.vt;
-  p.B = B;
-  p.Hkv = Hkv;
-  p.L = L;
-  p.kv_stride = kv_stride;
-  p.n_tiles = n_tiles;
-  p.retry_count = a.retry_count;
-  p.block_table = pg.block_table;
-  p.max_pages = pg.max_pages;
-  p.page_shift = pg.page_shift;
-  p.n_pages = pg.n_pages;
-  if ((long long)B * Hkv > 65535) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(vt_prep_kernel, dim3(n_tiles, B * Hkv), dim3(256), 0, stream, p);
-  return hipGetLastError();
 }
 
 // L: keys of the call; the queries are rows q_start .. q_start + Lq - 1
@@ -967,14 +848,9 @@ static void fill_geometry(PrefillArgs& a, int B, int Hq, int Hkv, int L, int q_s
   a.slack = slack;
 }
 
-// The fused and vanilla modes: the fast pass over the grid, then the checked
-// pass over the blocks it listed (same grid size; the rest exit at once).
 template <int MODE, bool PAGED = false>
-static hipError_t launch_fast_then_checked(const PrefillArgs& a, dim3 grid, hipStream_t stream) {
-  hipLaunchKernelGGL((prefill_kernel<MODE, false, PAGED>), grid, dim3(kPfThreads), 0, stream, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((prefill_kernel<MODE, true, PAGED>), grid, dim3(kPfThreads), 0, stream, a);
+static hipError_t launch_blocks(const PrefillArgs& a, dim3 grid, hipStream_t stream) {
+  hipLaunchKernelGGL((prefill_kernel<MODE, PAGED>), grid, dim3(kPfThreads), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -983,16 +859,16 @@ static hipError_t launch_attn(int mode, const PrefillArgs& a, hipStream_t stream
   if (nwg > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)nwg);
   if (a.block_table != nullptr) {  // paged caches: the chunk entry points only
-    if (mode == kModeFused) return launch_fast_then_checked<kModeFused, true>(a, grid, stream);
-    if (mode == kModeVanilla) return launch_fast_then_checked<kModeVanilla, true>(a, grid, stream);
+    if (mode == kModeFused) return launch_blocks<kModeFused, true>(a, grid, stream);
+    if (mode == kModeVanilla) return launch_blocks<kModeVanilla, true>(a, grid, stream);
     return hipErrorInvalidValue;
   }
   switch (mode) {
-    case kModeFused: return launch_fast_then_checked<kModeFused>(a, grid, stream);
-    case kModeVanilla: return launch_fast_then_checked<kModeVanilla>(a, grid, stream);
-    case kModeWinA: return launch_fast_then_checked<kModeWinA>(a, grid, stream);
-    case kModeWinB: return launch_fast_then_checked<kModeWinB>(a, grid, stream);
-    case kModeWinC: return launch_fast_then_checked<kModeWinC>(a, grid, stream);
+    case kModeFused: return launch_blocks<kModeFused>(a, grid, stream);
+    case kModeVanilla: return launch_blocks<kModeVanilla>(a, grid, stream);
+    case kModeWinA: return launch_blocks<kModeWinA>(a, grid, stream);
+    case kModeWinB: return launch_blocks<kModeWinB>(a, grid, stream);
+    case kModeWinC: return launch_blocks<kModeWinC>(a, grid, stream);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1006,19 +882,17 @@ hipError_t launch_prefill_chunk(bool bifocal, const uint16_t* q, const uint16_t*
                                 const float2* rtable, const uint32_t* table16,
                                 const uint32_t* rtable16, int freq_map, int B, int Hq, int Hkv,
                                 int L, int q_start, int Lq, int kv_stride, int G, int w0,
-                                float slack, void* ws, hipStream_t stream, hipEvent_t ev0,
+                                float slack, hipStream_t stream, hipEvent_t ev0,
                                 hipEvent_t ev1, const int32_t* block_table, int max_pages,
                                 int page_shift, int n_pages) {
   PrefillArgs a = {};
   fill_geometry(a, B, Hq, Hkv, L, q_start, Lq, slack);
-  hipError_t e = launch_prep(k, v, table, rtable, table16, rtable16, freq_map, B, Hkv, L,
-                             kv_stride, G, ws, true, a, stream,
-                             Paging{block_table, max_pages, page_shift, n_pages});
-  if (e != hipSuccess) return e;
-  a.q = q;
+  fill_inputs(a, q, k, v, table, rtable, table16, rtable16, freq_map, kv_stride, G,
+              Paging{block_table, max_pages, page_shift, n_pages});
   a.o = o;
   a.lse = lse;
   a.w0 = bifocal ? w0 : INT_MAX;
+  hipError_t e = hipSuccess;
   if (ev0 != nullptr && (e = hipEventRecord(ev0, stream)) != hipSuccess) return e;
   e = launch_attn(bifocal ? kModeFused : kModeVanilla, a, stream);
   if (e == hipSuccess && ev1 != nullptr) e = hipEventRecord(ev1, stream);
@@ -1035,25 +909,15 @@ hipError_t launch_prefill_literal(const uint16_t* q, const uint16_t* k, const ui
   const size_t rows = (size_t)B * L * Hq;
   float* o3 = (float*)ws;
   float* lse3 = o3 + 3 * rows * kHeadDim;
-  void* images = (unsigned char*)ws + 3 * rows * kHeadDim * sizeof(float) +
-                 round256(3 * rows * sizeof(float));
   PrefillArgs a = {};
   fill_geometry(a, B, Hq, Hkv, L, 0, L, slack);
-  // each window runs as the fused call does: a fast pass, then the checked
-  // rerun of the blocks it lists.  The passes count their blocks in counters
-  // of their own (all zeroed by the prep kernel) and share the list, which
-  // each pass's rerun has read before the next pass writes it (one stream).
-  hipError_t e = launch_prep(k, v, table, rtable, table16, rtable16, freq_map, B, Hkv, L, L, G,
-                             images, true, a, stream);
-  if (e != hipSuccess) return e;
-  a.q = q;
-  int* const counters = a.retry_count;
+  fill_inputs(a, q, k, v, table, rtable, table16, rtable16, freq_map, L, G);
+  hipError_t e = hipSuccess;
   const int modes[3] = {kModeWinA, kModeWinB, kModeWinC};
   for (int x = 0; x < 3; ++x) {
     a.o32 = o3 + (size_t)x * rows * kHeadDim;
     a.lse = lse3 + (size_t)x * rows;
     a.w0 = modes[x] == kModeWinB ? INT_MAX : w0;
-    a.retry_count = counters + x;
     e = launch_attn(modes[x], a, stream);
     if (e != hipSuccess) return e;
   }
@@ -1077,8 +941,9 @@ hipError_t launch_prefill_literal(const uint16_t* q, const uint16_t* k, const ui
 // Sequence s of a packed batch holds rows cu[s] .. cu[s + 1] - 1 of q, k, v
 // and o.  Its bounds are clamped into [0, T] (a non-increasing entry gives an
 // empty sequence) and its length to max_len.  The work lists hold one
-// (seq0, L, index, tile0) per query block (index = block, last block first)
-// and per key tile (index = tile); their sizes nq = ceil(T / BQ) + B and
+// (seq0, L, index, first tile) per query block (index = block, last block
+// first) and, for the frequency map's tables, per key tile (index = tile);
+// their sizes nq = ceil(T / BQ) + B and
 // nt = ceil(T / 64) + B bound the totals of any well-formed cu.  A sequence
 // whose entries would run past either list (possible only for malformed
 // cu) gets none: its output rows are left untouched.  Every list entry is
@@ -1087,7 +952,7 @@ struct PlanArgs {
   const int32_t* cu;
   int B, T, max_len, BQ;
   int4* qwork;
-  int4* twork;
+  int4* twork;  // nullptr: no tile list is wanted
   int nq, nt;
 };
 
@@ -1141,7 +1006,7 @@ __global__ __launch_bounds__(kPlanThreads) void varlen_plan_kernel(PlanArgs a) {
       a.qwork[base_q + e] = fits(j) ? int4{s_seq0[j], s_len[j], (int)(nb - 1 - i), (int)toff}
                                     : int4{0, 0, 0, 0};
     }
-    for (long long e = t; e < tot_t && base_t + e < a.nt; e += kPlanThreads) {
+    for (long long e = t; a.twork != nullptr && e < tot_t && base_t + e < a.nt; e += kPlanThreads) {
       const int j = owner(inc_t, e);
       const int nk = (s_len[j] + kPfBK - 1) / kPfBK;
       const long long i = e - (inc_t[j] - nk);
@@ -1154,7 +1019,7 @@ __global__ __launch_bounds__(kPlanThreads) void varlen_plan_kernel(PlanArgs a) {
   }
   for (long long e = min(base_q, (long long)a.nq) + t; e < a.nq; e += kPlanThreads)
     a.qwork[e] = int4{0, 0, 0, 0};
-  for (long long e = min(base_t, (long long)a.nt) + t; e < a.nt; e += kPlanThreads)
+  for (long long e = min(base_t, (long long)a.nt) + t; a.twork != nullptr && e < a.nt; e += kPlanThreads)
     a.twork[e] = int4{0, 0, 0, 0};
 }
 
@@ -1164,19 +1029,17 @@ static void varlen_sizes(int B, int T, int g, long long* nq, long long* nt) {
   *nt = ((long long)T + kPfBK - 1) / kPfBK + B;
 }
 
-// Scratch of a packed call: the V^T images of nt tiles per kv head (kv head
-// h's at h * nt), the query-block and tile work lists, the rerun counter and
-// list, then (frequency map only) the per-sequence remote tables, fp32 and
-// bf16, one row per token.
-static size_t varlen_lists_end(int B, int T, int Hq, int Hkv) {
+// Scratch of a packed call: the query-block work list, then (frequency map
+// only) the tile list and the per-sequence remote tables, fp32 and bf16, one
+// row per token.
+static size_t varlen_lists_end(int B, int T, int Hq, int Hkv, bool freq) {
   long long nq, nt;
   varlen_sizes(B, T, Hq / Hkv, &nq, &nt);
-  return (size_t)Hkv * nt * kTileBytes + (size_t)(nq + nt) * sizeof(int4) + retry_bytes(nq * Hkv);
+  return (size_t)(nq + (freq ? nt : 0)) * sizeof(int4);
 }
 
-size_t prefill_varlen_workspace_bytes(bool bifocal, int B, int T, int Hq, int Hkv, bool freq) {
-  (void)bifocal;  // one V^T image set either way
-  const size_t base = varlen_lists_end(B, T, Hq, Hkv);
+size_t prefill_varlen_workspace_bytes(int B, int T, int Hq, int Hkv, bool freq) {
+  const size_t base = varlen_lists_end(B, T, Hq, Hkv, freq);
   if (!freq) return base;
   return round256(base) + (size_t)T * kHalf * (sizeof(float2) + sizeof(uint32_t));
 }
@@ -1197,23 +1060,12 @@ hipError_t launch_prefill_varlen(bool bifocal, const uint16_t* q, const uint16_t
   varlen_sizes(B, T, Hq / Hkv, &nq, &nt);
   if (nq * Hkv > 0x7fffffffLL || nt > 0x7fffffffLL || Hkv > 65535)
     return hipErrorInvalidConfiguration;
-  const size_t img = (size_t)Hkv * nt * (kTileBytes / 2);  // bf16 elements of the V^T images
+  const bool freq = bifocal && freq_og != nullptr;
   PrefillArgs a = {};
   fill_geometry(a, 1, Hq, Hkv, max_len, 0, T, slack);
-  a.k = k;
-  a.vt = (const uint16_t*)ws;
-  int4* qwork = (int4*)((uint16_t*)ws + img);
-  int4* twork = qwork + nq;
-  a.retry_count = (int*)(twork + nt);
-  a.retry_list = a.retry_count + 64;
-  a.n_tiles = (int)nt;
-  a.table = table;
-  a.rtable = table;
-  a.table16 = table16;
-  a.rtable16 = table16;
-  a.freq_map = 0;
-  a.gdiv = make_fastdiv(1);
-  a.q = q;
+  fill_inputs(a, q, k, v, table, table, table16, table16, 0, T, 1);
+  int4* qwork = (int4*)ws;
+  int4* twork = freq ? qwork + nq : nullptr;
   a.o = o;
   a.lse = lse;
   a.w0 = bifocal ? w0 : INT_MAX;
@@ -1233,8 +1085,8 @@ hipError_t launch_prefill_varlen(bool bifocal, const uint16_t* q, const uint16_t
   hipLaunchKernelGGL(varlen_plan_kernel, dim3(1), dim3(kPlanThreads), 0, stream, pl);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (bifocal && freq_og != nullptr) {  // each sequence's frequency-map rows, at its own rows
-    unsigned char* rt = (unsigned char*)ws + round256(varlen_lists_end(B, T, Hq, Hkv));
+  if (freq) {  // each sequence's frequency-map rows, at its own rows
+    unsigned char* rt = (unsigned char*)ws + round256(varlen_lists_end(B, T, Hq, Hkv, true));
     float2* rt32 = (float2*)rt;
     uint32_t* rt16 = (uint32_t*)(rt + (size_t)T * kHalf * sizeof(float2));
     e = launch_packed_freq_table(twork, (int)nt, w_pre, freq_og, rt32, rt16, stream);
@@ -1245,23 +1097,10 @@ hipError_t launch_prefill_varlen(bool bifocal, const uint16_t* q, const uint16_t
     a.rtab_packed = 1;
   }
 
-  PrepArgs p = {};
-  p.v = v;
-  p.vt = (uint16_t*)a.vt;
-  p.B = 1;
-  p.Hkv = Hkv;
-  p.L = max_len;
-  p.kv_stride = T;
-  p.n_tiles = (int)nt;
-  p.twork = twork;
-  p.retry_count = a.retry_count;
-  hipLaunchKernelGGL(vt_prep_kernel, dim3((unsigned)nt, Hkv), dim3(256), 0, stream, p);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-
   if (ev0 != nullptr && (e = hipEventRecord(ev0, stream)) != hipSuccess) return e;
   const dim3 grid((unsigned)(nq * Hkv));
-  e = bifocal ? launch_fast_then_checked<kModeFused>(a, grid, stream)
-              : launch_fast_then_checked<kModeVanilla>(a, grid, stream);
+  e = bifocal ? launch_blocks<kModeFused>(a, grid, stream)
+              : launch_blocks<kModeVanilla>(a, grid, stream);
   if (e == hipSuccess && ev1 != nullptr) e = hipEventRecord(ev1, stream);
   return e;
 }
