@@ -31,9 +31,10 @@
  *      - the RoPE cos/sin table (per device and rope_theta, grown by
  *        doubling to cover the call's positions): every prefill and decode
  *        entry point; growing allocates and waits for `stream`;
- *      - the packed-prefill scratch (per device and stream): the _varlen
- *        forms; growing waits for `stream`, frees the old buffer and
- *        allocates;
+ *      - the prefill scratch (per device and stream): the _varlen forms, and
+ *        of jl_bifocal_prefill, jl_rope_attention, their _map and _chunk forms
+ *        the calls whose query blocks leave CUs idle (see there); growing
+ *        waits for `stream`, frees the old buffer and allocates;
  *      - the frequency-map table (one per device): jl_bifocal_prefill_map
  *        with JL_REMOTE_FREQ; a new (rope_theta, L, w_pretrained) waits for
  *        the whole device, then rebuilds the table in place, or in a buffer
@@ -97,7 +98,12 @@ int64_t jl_group_size(int64_t L, int64_t w_pretrained);
  * rotated to the view of the visit (R(k) x_k on the band, R(f(k)) x_k beyond
  * it, Sec. 3.2); the rotated tile is kept only in on-chip memory and no
  * rotated key is written anywhere.
- * One kernel launch, no scratch; q, k, v are only read.
+ * A call with fewer query blocks than CUs (a block is 256 / (Hq / Hkv) query
+ * positions of one sequence and kv head), or whose blocks make up a few whole
+ * waves of the CUs and a small rest, cuts the idle CUs' share of its blocks
+ * into parts of the key range and merges their fp32 states (133 KB per part, at
+ * most 16 parts a block, in the prefill scratch); others need no scratch.
+ * q, k, v are only read.
  */
 int jl_bifocal_prefill(const void* q, const void* k, const void* v, void* o, float* lse, int B,
                        int Hq, int Hkv, int L, int head_dim, double rope_theta, int w_pretrained,
@@ -146,7 +152,9 @@ int jl_bifocal_prefill_map(const void* q, const void* k, const void* v, void* o,
  * The call's sequence length is L = q_start + n_queries: G = max(1,
  * ceil(L / w_pretrained)) for every query of the chunk, as in a prefill of
  * length L, so the output equals rows q_start .. L - 1 of
- * jl_bifocal_prefill over the first L cache rows.  The caches are only read:
+ * jl_bifocal_prefill over the first L cache rows: bit for bit where neither
+ * call cuts its blocks (see there), and up to the order of the fp32 sums over
+ * the parts otherwise.  The caches are only read:
  * keys are rotated on chip per visit, as in jl_bifocal_prefill.  Requires 0 <= q_start, n_queries >= 1,
  * q_start + n_queries <= max_len; other requirements and errors as in
  * jl_bifocal_prefill.

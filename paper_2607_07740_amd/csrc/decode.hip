@@ -888,7 +888,7 @@ __global__ __launch_bounds__(256) void decode_reduce_batch_kernel(DecodeArgs a, 
 }
 
 // ---------------------------------------------------------------- launcher
-static int cu_count() {
+int cu_count() {
   static int cached[64] = {0};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;

@@ -23,9 +23,12 @@ hipError_t launch_prefill_chunk(bool bifocal, const uint16_t* q, const uint16_t*
                                 const float2* rtable, const uint32_t* table16,
                                 const uint32_t* rtable16, int freq_map, int B, int Hq, int Hkv,
                                 int L, int q_start, int Lq, int kv_stride, int G, int w0,
-                                float slack, hipStream_t stream, hipEvent_t ev0,
-                                hipEvent_t ev1, const int32_t* block_table, int max_pages,
-                                int page_shift, int n_pages);
+                                float slack, int n_cu, void* states, hipStream_t stream,
+                                hipEvent_t ev0, hipEvent_t ev1, const int32_t* block_table,
+                                int max_pages, int page_shift, int n_pages);
+size_t prefill_chunk_workspace_bytes(int n_cu, bool bifocal, int B, int Hq, int Hkv, int q_start,
+                                     int Lq, int w0);
+int cu_count();
 size_t prefill_varlen_workspace_bytes(int B, int T, int Hq, int Hkv, bool freq);
 hipError_t launch_prefill_varlen(bool bifocal, const uint16_t* q, const uint16_t* k,
                                  const uint16_t* v, uint16_t* o, float* lse, const float2* table,
@@ -278,8 +281,9 @@ int get_freq_table(double theta, int L, int w_pre, hipStream_t stream, Tables* o
   return JL_OK;
 }
 
-// ------------------------------------- packed prefill scratch, per stream
-// A packed call's work lists (and frequency-map tables).  One buffer per
+// ------------------------------------------- prefill scratch, per stream
+// A packed call's work lists (and frequency-map tables), or the states of a
+// call whose blocks are cut into parts.  One buffer per
 // (device, stream): calls on one stream are ordered, so they can share it; a
 // call that needs more waits for its stream before replacing it.
 struct Scratch {
@@ -404,12 +408,24 @@ int prefill_common(bool bifocal, const void* q, const void* k, const void* v, vo
       return ok();
     }
   }
+  // where the blocks of the call leave CUs idle they are cut into parts, whose
+  // states go to the stream's scratch
+  const int n_cu = literal ? 1 : jl::cu_count();  // 1: no block is cut (no library scratch)
+  void* states = nullptr;
+  std::unique_lock<std::mutex> launch_lock(g_prefill_mu, std::defer_lock);
+  const size_t state_bytes = jl::prefill_chunk_workspace_bytes(n_cu, use_bifocal, B, Hq, Hkv,
+                                                               q_start, Lq, w0);
+  if (state_bytes > 0) {
+    launch_lock.lock();
+    st = get_scratch(s, state_bytes, &states);
+    if (st != JL_OK) return st;
+  }
   hipEvent_t ev0, ev1;
   timing_events(0, &ev0, &ev1);
   hipError_t e = jl::launch_prefill_chunk(use_bifocal, (const uint16_t*)q, (const uint16_t*)k,
                                           (const uint16_t*)v, (uint16_t*)o, lse, tab.f32, rtab.f32,
                                           tab.f16, rtab.f16, freq_map, B, Hq, Hkv, L, q_start, Lq,
-                                          kv_stride, G, w0, slack, s, ev0, ev1,
+                                          kv_stride, G, w0, slack, n_cu, states, s, ev0, ev1,
                                           block_table, max_pages, page_shift, n_pages);
   if (e != hipSuccess) return hip_fail(e, "prefill launch");
   return ok();

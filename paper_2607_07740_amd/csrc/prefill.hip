@@ -43,8 +43,8 @@
 // above it, or more than 64 below it before anything was accumulated),
 // re-bases the tile and rescales the state.  So every probability stays below
 // 2^64.
+#include <algorithm>
 #include <climits>
-#include <type_traits>
 
 #include "jl_device.h"
 
@@ -114,6 +114,11 @@ struct PrefillArgs {
   // pages of at least 64 keys, so a tile lies in one page
   const int32_t* block_table;
   int max_pages, page_shift, n_pages;
+  // split blocks (see block_parts): the grid's first n_whole workgroups take
+  // one block each; the n_tail blocks behind them are cut into up to n_part
+  // parts, part-major, whose states meet in merge_parts_kernel
+  int n_blocks, n_whole, n_tail, n_part;
+  float* states;
 };
 
 // Most pages of one sequence a paged prefill block looks up (LDS table)
@@ -156,7 +161,7 @@ __device__ inline bool work_of(const PrefillArgs& a, int bid, bool fused, Work& 
   } else {
     int group;
     if ((n_groups & 7) == 0) {
-      const int work = (bid & 7) * (gridDim.x >> 3) + (bid >> 3);
+      const int work = (bid & 7) * (a.n_blocks >> 3) + (bid >> 3);
       group = work / a.n_qblocks;
       W.qblk = a.n_qblocks - 1 - (work - group * a.n_qblocks);
     } else {
@@ -218,15 +223,42 @@ __device__ inline void load_q_operand(const uint16_t* qrow, int half, const floa
 }
 
 
-// One query block.  SAFE = false: the fast pass.  It never waits on the
+// Visits of a fused (or, with w0 = INT_MAX, vanilla) block of queries q0 .. q1
+__host__ __device__ inline int block_visits(int q0, int q1, int w0) {
+  const VisitRanges vr = visit_ranges(q0, q1, w0, kPfBK);
+  return vr.n_r + (vr.n_kt - vr.kt_l);
+}
+
+// A block whose call leaves CUs idle is cut into parts of its visit list, at
+// least kMinPart visits each, that run as workgroups of their own: a 512-query
+// chunk has 64 blocks of 32/8 heads, a quarter of the CUs.  Each part leaves
+// its state (m, l, O) in memory, and merge_parts_kernel combines them with the
+// weights of Eq. (7).
+constexpr int kMinPart = 16;
+__device__ inline int block_parts(const PrefillArgs& a, const Work& W) {
+  const int q0 = W.q_start + W.qblk * a.BQ;
+  const int q1 = min(q0 + a.BQ, W.q_end) - 1;
+  return max(1, min(a.n_part, block_visits(q0, q1, W.w0) / kMinPart));
+}
+
+// State of one part: O, as [d / 4][row][4] floats so that a wave's stores and
+// the merge's loads are contiguous, then (m, l) per row.
+constexpr int kPartFloats = kPfRows * (kHeadDim + 2);
+__device__ inline float* part_state(const PrefillArgs& a, int tail_block, int part) {
+  return a.states + (size_t)(part * a.n_tail + tail_block) * kPartFloats;
+}
+
+// One query block, or with SPLIT its part `part` of `parts`, whose state goes
+// to `state` (parts > 1).  SAFE = false: the fast pass.  It never waits on the
 // softmax reference check; instead it records, without a branch, whether any
 // tile's probability sum exceeded 2^slack, and at the end whether a row's
 // total fell below 2^-slack.  A block with either writes nothing and returns
 // true; the kernel then runs it again with SAFE = true: the per-tile check,
 // which moves the reference as needed.  Every mode runs so.
-template <int MODE, bool SAFE, bool PAGED>
+template <int MODE, bool SAFE, bool PAGED, bool SPLIT>
 __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& W,
-                                              unsigned char* smem, int* s_bad, int* s_pages) {
+                                              unsigned char* smem, int* s_bad, int* s_pages,
+                                              int part, int parts, float* state) {
   constexpr bool CHECK_LATE = !SAFE;
   // The visit list has at most two segments: the fused kernel's remote tiles
   // (segment 1), then tiles [kt_l, n_kt) in one view, keeping 0 <= q - k <= w0
@@ -263,15 +295,24 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
   // ---- visit list: segment 1 = tiles [0, n_r), segment 2 = tiles [kt_l, n_kt)
   const VisitRanges vr = visit_ranges(q0, q1, w0, kPfBK);
   const int n_kt = vr.n_kt;
-  const int n_r = FUSED ? vr.n_r : 0;
-  const int kt_l = FROM_ZERO ? 0 : vr.kt_l;
-  const int n_steps = n_r + (n_kt - kt_l);
+  int n_r = FUSED ? vr.n_r : 0;
+  int kt_l = FROM_ZERO ? 0 : vr.kt_l;
+  int n_steps = n_r + (n_kt - kt_l);
+  int kt_r = 0;  // segment 1's first tile
+  if constexpr (SPLIT) {  // entries e0 .. e1 - 1 of the list
+    const int e0 = (int)((long long)n_steps * part / parts);
+    const int e1 = (int)((long long)n_steps * (part + 1) / parts);
+    kt_r = e0;
+    kt_l += max(e0 - n_r, 0);
+    n_r = min(max(n_r - e0, 0), e1 - e0);
+    n_steps = e1 - e0;
+  }
 
   // ---- staging.  For list entry j each wave copies its 8 keys of the V tile
   // into buffer jb & 1, and rotates the same 8 keys of the raw K tile, read
   // from memory, into the rotated buffer of that parity.
   const uint32_t smem_base = lds_addr(smem);
-  auto tile_of = [&](int j) __attribute__((always_inline)) { return j < n_r ? j : kt_l + (j - n_r); };
+  auto tile_of = [&](int j) __attribute__((always_inline)) { return j < n_r ? kt_r + j : kt_l + (j - n_r); };
   // j's view: remote (R(f(k)), Eq. (3), or the frequency map's table at k) or base (R(k))
   auto is_remote = [&](int j) __attribute__((always_inline)) { return REMOTE2 || (FUSED && j < n_r); };
   // Scalar description of list entry j, formed a visit before its
@@ -454,7 +495,7 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
   auto seg1_bounds = [&](int& lo, int& hi) __attribute__((always_inline)) {
     const long long x = (long long)q0 - (kPfBK - 1) - w0;  // tile j fully remote: 64 j < x
     lo = 0;
-    hi = (x > 0 ? (int)((x + kPfBK - 1) / kPfBK) : 0) - 1;
+    hi = (x > 0 ? (int)((x + kPfBK - 1) / kPfBK) : 0) - 1 - kt_r;
   };
   auto seg2_bounds = [&](int& lo, int& hi) __attribute__((always_inline)) {
     const long long y = (long long)q1 - w0;
@@ -692,6 +733,8 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
     int lo = 0, hi = 0;
     if (!SAFE) seg1_bounds(lo, hi);
     segment(0, n_r, lo, hi, vent, pend);
+  }
+  if (FUSED && n_r > 0 && (!SPLIT || n_r < n_steps)) {
     // segment 2 in the base view: its first tile, already rotated to the base
     // view (buffer n_r & 1, not overwritten since), is scored again with the
     // base-rotated query operand
@@ -712,6 +755,22 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
     if (late_bad != 0 && lane == 0) *s_bad = 1;
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(*s_bad) != 0) return true;
+  }
+  if (SPLIT && parts > 1) {  // rows past the last query repeat it: their states are not read
+    asm volatile("" : "+s"(state));  // or the addresses are formed, and kept, before the loops
+    const uint32_t lane4 = (uint32_t)(hl32 * kPfRows + row);
+#pragma unroll
+    for (int db = 0; db < 4; ++db) {
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        f32x4 t;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) t[jj] = acc_o[db][4 * q4 + jj];
+        ((f32x4*)state)[(8 * db + 2 * q4) * kPfRows + lane4] = t;
+      }
+    }
+    if (hl32 == 0) ((float2*)(state + kPfRows * kHeadDim))[row] = make_float2(m_ref, l_tot);
+    return false;
   }
   if (row_valid) {
     const float inv = 1.f / l_tot;
@@ -736,18 +795,71 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
   return false;
 }
 
-template <int MODE, bool PAGED = false>
+template <int MODE, bool PAGED = false, bool SPLIT = false>
 __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
   // LDS: rotated K tiles and V tiles, two buffers each
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kSmemBytes];
   __shared__ int s_bad;
   __shared__ int s_pages[PAGED ? kMaxSeqPages : 1];  // paged caches: the sequence's pages
-  Work W;
-  if (!work_of(a, blockIdx.x, MODE == kModeFused, W)) return;  // uniform, before any barrier
-  if (prefill_block<MODE, false, PAGED>(a, W, smem, &s_bad, s_pages)) {
-    __syncthreads();  // every wave is done with the fast pass's tiles
-    prefill_block<MODE, true, PAGED>(a, W, smem, &s_bad, s_pages);
+  int bid = blockIdx.x, part = 0, parts = 1;
+  float* state = nullptr;
+  const bool tail = SPLIT && bid >= a.n_whole;
+  if (tail) {
+    part = (bid - a.n_whole) / a.n_tail;
+    bid -= part * a.n_tail;
   }
+  Work W;
+  if (!work_of(a, bid, MODE == kModeFused, W)) return;  // uniform, before any barrier
+  if (tail) {
+    parts = block_parts(a, W);
+    if (part >= parts) return;
+    state = part_state(a, bid - a.n_whole, part);
+  }
+  if (prefill_block<MODE, false, PAGED, SPLIT>(a, W, smem, &s_bad, s_pages, part, parts, state)) {
+    __syncthreads();  // every wave is done with the fast pass's tiles
+    prefill_block<MODE, true, PAGED, SPLIT>(a, W, smem, &s_bad, s_pages, part, parts, state);
+  }
+}
+
+// The parts of each tail block, combined per row:
+//   M = max m, O = sum 2^(m - M) O~ / sum 2^(m - M) l,  lse = ln 2 (M + log2 of that sum).
+// Workgroup: 32 rows of a block; thread -> row tid % 32, channels 16 (tid / 32) .. + 15.
+// Bound by reading the states: 34 MB (16384 rows in 4 parts) in about 10 us.
+__global__ __launch_bounds__(256) void merge_parts_kernel(PrefillArgs a) {
+  const int tb = blockIdx.x;
+  Work W;
+  if (!work_of(a, a.n_whole + tb, true, W)) return;
+  const int parts = block_parts(a, W);
+  if (parts <= 1) return;  // written by the block itself
+  const int row = 32 * blockIdx.y + (threadIdx.x & 31);
+  const int dg = threadIdx.x >> 5;
+  const int hl = row / a.BQ;
+  const int qpos = W.q_start + W.qblk * a.BQ + (row - hl * a.BQ);
+  if (qpos >= W.q_end) return;
+  float M = -INFINITY;
+  for (int s = 0; s < parts; ++s) {
+    const float2 ml = ((const float2*)(part_state(a, tb, s) + kPfRows * kHeadDim))[row];
+    if (ml.y != 0.f) M = fmaxf(M, ml.x);  // a part without keys of this row has no weight
+  }
+  float den = 0.f;
+  f32x4 acc[4] = {};
+  for (int s = 0; s < parts; ++s) {
+    const float* st = part_state(a, tb, s);
+    const float2 ml = ((const float2*)(st + kPfRows * kHeadDim))[row];
+    if (ml.y == 0.f) continue;
+    const float w = fast_exp2(ml.x - M);
+    den += w * ml.y;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] += w * ((const f32x4*)st)[(4 * dg + i) * kPfRows + row];
+  }
+  const int hd = W.kvh * a.g + hl;
+  const int qr = qpos - W.q_start;
+  const float inv = 1.f / den;
+  uint16_t* o = a.o + ((W.row_base + qr) * a.Hq + hd) * kHeadDim + 16 * dg;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) *(bf16x4*)(o + 4 * i) = __builtin_convertvector(acc[i] * inv, bf16x4);
+  if (a.lse != nullptr && dg == 0)
+    a.lse[W.lse_base + (size_t)hd * a.Lq + qr] = (M + log2f(den)) * 0.69314718055994531f;
 }
 
 // ------------------------------------------------------ Eq. (7) merge kernel
@@ -844,6 +956,7 @@ static void fill_geometry(PrefillArgs& a, int B, int Hq, int Hkv, int L, int q_s
   a.g = Hq / Hkv;
   a.BQ = kPfRows / a.g;
   a.n_qblocks = (Lq + a.BQ - 1) / a.BQ;
+  a.n_blocks = a.n_qblocks * B * Hkv;  // dense batches (a packed one reads its plan)
   a.q_scale = 1.4426950408889634f / sqrtf((float)kHeadDim);
   a.slack = slack;
 }
@@ -852,6 +965,72 @@ template <int MODE, bool PAGED = false>
 static hipError_t launch_blocks(const PrefillArgs& a, dim3 grid, hipStream_t stream) {
   hipLaunchKernelGGL((prefill_kernel<MODE, PAGED>), grid, dim3(kPfThreads), 0, stream, a);
   return hipGetLastError();
+}
+
+template <int MODE, bool PAGED>
+static hipError_t launch_split_blocks(const PrefillArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)(a.n_whole + a.n_tail * a.n_part));
+  hipLaunchKernelGGL((prefill_kernel<MODE, PAGED, true>), grid, dim3(kPfThreads), 0, stream, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(merge_parts_kernel, dim3(a.n_tail, kPfRows / 32), dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
+
+// How a fused or vanilla call of Lq queries behind q_start is cut; times are in
+// tile visits, of about 1.5 us.  A workgroup fills a CU, so blocks run in waves
+// of n_cu.  Blocks of about equal length (a chunk far into a sequence) are
+// only cut where they make up the last, partial wave; blocks of very
+// different lengths (a prefill from position 0) fill the CUs among themselves
+// unless there are fewer blocks than CUs.  A part costs kPartCost visits to
+// start, the merge kMergeCost to launch and kStateCost per part to write and
+// read its state; the cheapest number of parts is taken if it saves a tenth.
+// Measured, whole blocks against parts: 512 queries behind 36011 keys, 32/8
+// heads, 896 -> 357 us (64 blocks in 4 parts: 322 us and a 9 us merge); 128
+// behind 30000 713 -> 102; 1024 behind 49976, 16/8 heads, 1242 -> 490; 3000
+// behind 17000 (375 blocks: 256 whole, 119 in 2 parts) 967 -> 867; a prefill of
+// 8192, 4/1 heads, 195 -> 125.
+struct PrefillSplit {
+  int n_whole, n_tail, n_part;  // n_part = 1: no block is cut
+};
+
+static PrefillSplit prefill_split(int n_cu, long long n_blocks, int q_start, int Lq, int BQ,
+                                  int w0) {
+  constexpr double kPartCost = 4, kMergeCost = 5, kStateCost = 0.044;
+  constexpr int kMaxParts = 16;
+  PrefillSplit none = {(int)n_blocks, 0, 1};
+  const int n_qb = (Lq + BQ - 1) / BQ;
+  const int q_last = q_start + (n_qb - 1) * BQ;
+  const int n_max = block_visits(q_last, q_start + Lq - 1, w0);
+  const int n_min = block_visits(q_start, std::min(q_start + BQ, q_start + Lq) - 1, w0);
+  const bool even = n_min >= 0.8 * n_max;
+  if (n_blocks >= n_cu && (!even || n_blocks > 4LL * n_cu)) return none;
+  const int tail = (int)(n_blocks % n_cu);
+  if (tail == 0) return none;
+  PrefillSplit best = none;
+  double t_best = 0.9 * (n_max + kPartCost);
+  for (int s = 2; s <= kMaxParts && n_max / s >= kMinPart; ++s) {
+    const double part = (double)n_max / s + kPartCost;
+    const double waves = even ? (double)(((long long)tail * s + n_cu - 1) / n_cu) * part
+                              : 1.2 * tail * (0.5 * (n_min + n_max) + s * kPartCost) / n_cu;
+    const double t = std::max(part, waves) + kMergeCost + kStateCost * tail * s;
+    if (t < t_best) {
+      t_best = t;
+      best = PrefillSplit{(int)n_blocks - tail, tail, s};
+    }
+  }
+  return best;
+}
+
+// Bytes of scratch a call needs for the states of its parts (0: no block is cut)
+static size_t split_bytes(const PrefillSplit& sp) {
+  return sp.n_part > 1 ? (size_t)sp.n_tail * sp.n_part * kPartFloats * sizeof(float) : 0;
+}
+size_t prefill_chunk_workspace_bytes(int n_cu, bool bifocal, int B, int Hq, int Hkv, int q_start,
+                                     int Lq, int w0) {
+  const int BQ = kPfRows / (Hq / Hkv);
+  const long long n_blocks = (long long)((Lq + BQ - 1) / BQ) * B * Hkv;
+  return split_bytes(prefill_split(n_cu, n_blocks, q_start, Lq, BQ, bifocal ? w0 : INT_MAX));
 }
 
 static hipError_t launch_attn(int mode, const PrefillArgs& a, hipStream_t stream) {
@@ -882,9 +1061,9 @@ hipError_t launch_prefill_chunk(bool bifocal, const uint16_t* q, const uint16_t*
                                 const float2* rtable, const uint32_t* table16,
                                 const uint32_t* rtable16, int freq_map, int B, int Hq, int Hkv,
                                 int L, int q_start, int Lq, int kv_stride, int G, int w0,
-                                float slack, hipStream_t stream, hipEvent_t ev0,
-                                hipEvent_t ev1, const int32_t* block_table, int max_pages,
-                                int page_shift, int n_pages) {
+                                float slack, int n_cu, void* states, hipStream_t stream,
+                                hipEvent_t ev0, hipEvent_t ev1, const int32_t* block_table,
+                                int max_pages, int page_shift, int n_pages) {
   PrefillArgs a = {};
   fill_geometry(a, B, Hq, Hkv, L, q_start, Lq, slack);
   fill_inputs(a, q, k, v, table, rtable, table16, rtable16, freq_map, kv_stride, G,
@@ -894,7 +1073,20 @@ hipError_t launch_prefill_chunk(bool bifocal, const uint16_t* q, const uint16_t*
   a.w0 = bifocal ? w0 : INT_MAX;
   hipError_t e = hipSuccess;
   if (ev0 != nullptr && (e = hipEventRecord(ev0, stream)) != hipSuccess) return e;
-  e = launch_attn(bifocal ? kModeFused : kModeVanilla, a, stream);
+  const PrefillSplit sp = prefill_split(n_cu, a.n_blocks, q_start, Lq, a.BQ, a.w0);
+  if (sp.n_part > 1) {
+    a.n_whole = sp.n_whole;
+    a.n_tail = sp.n_tail;
+    a.n_part = sp.n_part;
+    a.states = (float*)states;
+    const bool paged = block_table != nullptr;
+    e = bifocal ? (paged ? launch_split_blocks<kModeFused, true>(a, stream)
+                         : launch_split_blocks<kModeFused, false>(a, stream))
+                : (paged ? launch_split_blocks<kModeVanilla, true>(a, stream)
+                         : launch_split_blocks<kModeVanilla, false>(a, stream));
+  } else {
+    e = launch_attn(bifocal ? kModeFused : kModeVanilla, a, stream);
+  }
   if (e == hipSuccess && ev1 != nullptr) e = hipEventRecord(ev1, stream);
   return e;
 }

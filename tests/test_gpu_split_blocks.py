@@ -1,0 +1,56 @@
+"""Prefill calls with fewer query blocks than CUs: their blocks are cut into
+parts of the key range (at least 16 tile visits each) whose states a second
+kernel merges.  Checked against the fp64 oracle, and the paged chunk against
+the dense one bit for bit (both are cut alike)."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2607_07740_amd import api, synth
+from parity_util import assert_close, say, to_dev, to_f64
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rescale", [None, 3.0])
+@pytest.mark.parametrize("P,n,B,Hkv,g,w_pre,w0", [
+    (4000, 64, 1, 1, 4, 1024, 300),    # one block, parts on both sides of the view switch
+    (3000, 300, 2, 2, 1, 700, 4000),   # the band covers every key: no remote part
+    (2500, 1, 1, 2, 8, 8192, 100),     # one query, G = 1: the vanilla kernel
+    (5003, 129, 1, 2, 2, 600, 0),      # ragged ends, w_local = 0
+    (0, 4100, 1, 1, 8, 2048, 500),     # a whole prefill whose blocks differ in length
+    (1100, 40, 1, 1, 1, 512, 64),      # too short to cut: one part
+])
+def test_split_blocks(P, n, B, Hkv, g, w_pre, w0, rescale):
+    """With the rescale bound lowered to 2^3 every part runs the checked pass,
+    whose parts carry different softmax references into the merge."""
+    T, Hq, page = P + n, g * Hkv, 64
+    q, k, v = synth.prefill_inputs(B, Hq, Hkv, T, 128, seed=T + g, outlier_channels=8)
+    pages = (T + page - 1) // page
+    pad = [(0, 0), (0, pages * page - T), (0, 0), (0, 0)]
+    kp, vp = (np.pad(x, pad, constant_values=0x7FC0) for x in (k, v))  # NaN past the sequence
+    kd, vd = to_dev(kp), to_dev(vp)
+    table = torch.arange(B * pages, dtype=torch.int32, device="cuda").view(B, pages)
+    kw = dict(q_start=P, w_pretrained=w_pre, w_local=w0, want_lse=True)
+    old = api.debug_prefill_rescale_log2(rescale) if rescale else None
+    try:
+        say("split blocks P=%d n=%d g=%d rescale=%s" % (P, n, g, rescale))
+        out, lse = api.prefill_chunk(to_dev(q[:, P:]), kd, vd, **kw)
+        say("split blocks, paged")
+        pg, pl = api.prefill_chunk_paged(to_dev(q[:, P:]), kd.view(-1, page, Hkv, 128),
+                                         vd.view(-1, page, Hkv, 128), table, **kw)
+        torch.cuda.synchronize()
+    finally:
+        if rescale:
+            api.debug_prefill_rescale_log2(old)
+    assert torch.equal(out.view(torch.int16), pg.view(torch.int16))
+    assert torch.equal(lse.view(torch.int32), pl.view(torch.int32))
+    pos = sorted(set(range(P, T, max(1, n // 40))) | {T - 1})
+    rows = np.array([[b, h, x] for b in range(B) for h in range(Hq) for x in pos], dtype=np.int64)
+    want, want_lse, _ = O.prefill_rows(q, k, v, rows, theta=1e6, w_pretrained=w_pre, w_local=w0,
+                                       want_lse=True)
+    assert_close(to_f64(out)[rows[:, 0], rows[:, 2] - P, rows[:, 1]], want, what="split blocks")
+    assert np.isfinite(to_f64(out)).all()
+    assert_close(lse.cpu().numpy()[rows[:, 0], rows[:, 1], rows[:, 2] - P], want_lse, max_abs=5e-2,
+                 mean_abs=5e-3, what="split lse")
