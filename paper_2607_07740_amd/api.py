@@ -135,10 +135,26 @@ def _check(status: int) -> None:
                            L.jl_last_error().decode())
 
 
+_torch = None
+
+
+def _t():
+    """The torch module, imported at the first call that takes tensors."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    """hipStream_t of the given stream, else of the current device's current one."""
+    if stream is not None:
+        return stream.cuda_stream
+    # the raw handle: building a Stream object for it takes 3 us, a fifth of a
+    # small decode call's time on the host
+    c = _t()._C
+    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
 
 
 def _dev(t, name, dtype=None, shape=None, device=None):
@@ -146,35 +162,31 @@ def _dev(t, name, dtype=None, shape=None, device=None):
     through raw pointers, so a caller-supplied output must have exactly the
     shape the call writes (shape), and every tensor must sit on the query's
     device (device)."""
-    import torch
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, _t().Tensor) or not t.is_cuda:
         raise TypeError("%s must be a CUDA (HIP) tensor" % name)
     if dtype is not None and t.dtype != dtype:
         raise TypeError("%s must be %s, got %s" % (name, dtype, t.dtype))
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError("%s must have shape %s, got %s" % (name, tuple(shape), tuple(t.shape)))
     if device is not None and t.device != device:
         raise ValueError("%s is on %s, the query on %s" % (name, t.device, device))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _bf16(t, name, q, shape=None):
     """A bf16 tensor of the call, on q's device."""
-    import torch
-    return _dev(t, name, torch.bfloat16, shape, q.device)
+    return _dev(t, name, _t().bfloat16, shape, q.device)
 
 
 def _f32(t, name, q, shape):
     """An optional fp32 output (None passes a null pointer), on q's device."""
-    import torch
-    return None if t is None else _dev(t, name, torch.float32, shape, q.device)
+    return None if t is None else _dev(t, name, _t().float32, shape, q.device)
 
 
 def _i32(t, name, q):
-    import torch
-    return _dev(t, name, torch.int32, None, q.device)
+    return _dev(t, name, _t().int32, None, q.device)
 
 
 def group_size(L: int, w_pretrained: int) -> int:
@@ -183,7 +195,7 @@ def group_size(L: int, w_pretrained: int) -> int:
 
 def _prefill(bifocal, q, k, v, w_pretrained, w_local, rope_theta, out, lse, want_lse, stream,
              remote_map="alias"):
-    import torch
+    torch = _t()
     B, L, Hq, D = q.shape
     Hkv = k.shape[2]
     if k.shape != (B, L, Hkv, D) or v.shape != k.shape:
@@ -228,7 +240,7 @@ def prefill_chunk(q, k_cache, v_cache, *, q_start: int, w_pretrained: int = 1, w
                   want_lse: bool = False, stream=None):
     """jl_bifocal_prefill_chunk / jl_rope_attention_chunk: q [B, n, Hq, 128] raw queries at
     positions q_start .. q_start + n - 1 over the raw caches [B, max_len, Hkv, 128]."""
-    import torch
+    torch = _t()
     B, n, Hq, D = q.shape
     _, max_len, Hkv, _ = k_cache.shape
     if k_cache.shape != (B, max_len, Hkv, D) or v_cache.shape != k_cache.shape:
@@ -256,7 +268,7 @@ def prefill_chunk_paged(q, k_pages, v_pages, block_table, *, q_start: int,
     """jl_bifocal_prefill_chunk_paged / jl_rope_attention_chunk_paged: q [B, n, Hq, 128] raw
     queries at positions q_start .. q_start + n - 1, pools [n_pages, page_size, Hkv, 128] raw,
     block_table int32 [B, max_pages] on the device."""
-    import torch
+    torch = _t()
     B, n, Hq, D = q.shape
     n_pages, page_size, Hkv, _ = k_pages.shape
     if k_pages.shape != (n_pages, page_size, Hkv, D) or v_pages.shape != k_pages.shape:
@@ -289,7 +301,7 @@ def prefill_varlen(q, k, v, cu_seqlens, *, max_seqlen: int, w_pretrained: int = 
     remote_map "freq" calls jl_bifocal_prefill_varlen_map with JL_REMOTE_FREQ (Sec. 4.5)."""
     if remote_map not in REMOTE_MAPS:
         raise ValueError("remote_map must be one of %s" % sorted(REMOTE_MAPS))
-    import torch
+    torch = _t()
     T, Hq, D = q.shape
     Hkv = k.shape[1]
     if k.shape != (T, Hkv, D) or v.shape != k.shape:
@@ -331,7 +343,7 @@ def bifocal_prefill_literal(q, k, v, *, w_pretrained: int, w_local: int, rope_th
     tensor of at least prefill_literal_workspace_bytes(...) bytes; after the
     call literal_window_states(workspace, ...) views the per-window results.
     """
-    import torch
+    torch = _t()
     B, L, Hq, D = q.shape
     Hkv = k.shape[2]
     if k.shape != (B, L, Hkv, D) or v.shape != k.shape:
@@ -354,7 +366,7 @@ def bifocal_prefill_literal(q, k, v, *, w_pretrained: int, w_local: int, rope_th
 
 def literal_window_states(workspace, B: int, Hq: int, L: int, head_dim: int = 128):
     """Views of a literal-prefill workspace: (O [3, B, L, Hq, D] fp32, LSE [3, B, Hq, L] fp32)."""
-    import torch
+    torch = _t()
     n_o = 3 * B * L * Hq * head_dim
     f = workspace[: 4 * (n_o + 3 * B * Hq * L)].view(torch.float32)
     return (f[:n_o].view(3, B, L, Hq, head_dim), f[n_o:].view(3, B, Hq, L))
@@ -366,7 +378,7 @@ def decode_workspace_bytes(B: int, Hq: int, Hkv: int, max_len: int, head_dim: in
 
 def _decode(bifocal, q, k_cache, v_cache, kv_lens, w_pretrained, w_local, rope_theta, out,
             workspace, stream):
-    import torch
+    torch = _t()
     B, Hq, D = q.shape
     _, max_len, Hkv, _ = k_cache.shape
     if k_cache.shape != (B, max_len, Hkv, D) or v_cache.shape != k_cache.shape:
@@ -395,7 +407,7 @@ def bifocal_decode_noalloc(q, k_cache, v_cache, kv_lens, *, w_pretrained: int, w
                            rope_theta: float = 1e6, out=None, stream=None):
     """jl_bifocal_decode_noalloc: jl_bifocal_decode without a workspace; the library's
     fixed per-device array holds the split states and the cos/sin table."""
-    import torch
+    torch = _t()
     B, Hq, D = q.shape
     _, max_len, Hkv, _ = k_cache.shape
     if k_cache.shape != (B, max_len, Hkv, D) or v_cache.shape != k_cache.shape:
@@ -420,7 +432,7 @@ def bifocal_decode(q, k_cache, v_cache, kv_lens, *, w_pretrained: int, w_local: 
     if remote_map == "alias":
         return _decode(True, q, k_cache, v_cache, kv_lens, w_pretrained, w_local, rope_theta,
                        out, workspace, stream)
-    import torch
+    torch = _t()
     if remote_map not in REMOTE_MAPS:
         raise ValueError("remote_map must be one of %s" % sorted(REMOTE_MAPS))
     B, Hq, D = q.shape
@@ -462,7 +474,7 @@ def decode_paged(q, k_pages, v_pages, block_table, kv_lens, *, w_pretrained: int
     pools [n_pages, page_size, Hkv, 128] raw, block_table int32 [B, max_pages],
     kv_lens int32 [B].  remote_map "freq" calls jl_bifocal_decode_paged_map with
     JL_REMOTE_FREQ (Sec. 4.5)."""
-    import torch
+    torch = _t()
     B, Hq, D = q.shape
     n_pages, page_size, Hkv, _ = k_pages.shape
     if k_pages.shape != (n_pages, page_size, Hkv, D) or v_pages.shape != k_pages.shape:
@@ -501,7 +513,7 @@ def decode_paged(q, k_pages, v_pages, block_table, kv_lens, *, w_pretrained: int
 
 def debug_schedule(lengths, positions, w_pretrained: int, stream=None):
     """jl_debug_schedule: device-computed G(L), f(x), Delta(x) (int32 CUDA tensors)."""
-    import torch
+    torch = _t()
     nl, npos = lengths.numel(), positions.numel()
     g = torch.empty(nl, dtype=torch.int32, device=lengths.device)
     f = torch.empty((nl, npos), dtype=torch.int32, device=lengths.device)
@@ -515,7 +527,7 @@ def debug_schedule(lengths, positions, w_pretrained: int, stream=None):
 
 def debug_prefill_tiles(L: int, Hq: int, Hkv: int, w_local: int, device="cuda", stream=None):
     """jl_debug_prefill_tiles: (classes int8 [n_qblocks, n_ktiles], block_q, block_k)."""
-    import torch
+    torch = _t()
     bq, bk, nq, nk = (ctypes.c_int(), ctypes.c_int(), ctypes.c_int(), ctypes.c_int())
     # first call with no buffer reports the geometry
     lib().jl_debug_prefill_tiles(L, Hq, Hkv, w_local, None, 0, ctypes.byref(bq),

@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <climits>
 #include <mutex>
+#include <type_traits>
 
 #include "jl_device.h"
 
@@ -67,14 +68,21 @@ struct DecodeArgs {
   int n_hgroups;  // groups of up to 4 kv heads
   int n_wg;       // workgroups per kv-head group
   int n_slots;    // state slots (see SplitRange)
-  // frequency-interpolation remote map (Sec. 4.5): omega_i and the ramp
-  // gamma_i of each frequency pair; every workgroup forms the cos/sin rows it
-  // needs from them and its sequence's length
-  double fomega[kHalf];
-  double fgamma[kHalf];
   int w_pre, w0;
   float q_scale;
 };
+
+// Frequency-interpolation remote map (Sec. 4.5): omega_i and the ramp gamma_i
+// of each frequency pair; every workgroup forms the cos/sin rows it needs from
+// them and its sequence's length.  Kernel arguments of that map's kernels only:
+// 1 KB that every other launch would carry too.
+struct FreqRamp {
+  double omega[kHalf];
+  double gamma[kHalf];
+};
+struct NoRamp {};
+template <bool FREQ>
+using RampOf = std::conditional_t<FREQ, FreqRamp, NoRamp>;
 
 __device__ inline int clamp_len(int n, int max_len) { return n < 1 ? 1 : (n > max_len ? max_len : n); }
 
@@ -296,12 +304,13 @@ __device__ inline float max_xor16_32(float x) {
 // reduced modulo 2 pi in fp64 (exact to ~1e-11 rad at 1.3e5 rad) and its sine
 // and cosine taken in fp32, within an ulp or two of the fp64 result rounded
 // to fp32.
-__device__ inline double freq_map_omega(const DecodeArgs& a, int n, int i) {
+__device__ inline double freq_map_omega(const FreqRamp& f, int w_pre, int n, int i) {
 #pragma clang fp contract(off)
-  const double om = a.fomega[i];
-  const double sc = fmax(1.0, (double)n / (double)a.w_pre);
-  return (1.0 - a.fgamma[i]) * om / sc + a.fgamma[i] * om;
+  const double om = f.omega[i];
+  const double sc = fmax(1.0, (double)n / (double)w_pre);
+  return (1.0 - f.gamma[i]) * om / sc + f.gamma[i] * om;
 }
+__device__ inline double freq_map_omega(const NoRamp&, int, int, int) { return 0.0; }
 __device__ inline float2 freq_map_cs(double omf, int pos) {
 #pragma clang fp contract(off)
   const double two_pi = 6.283185307179586476925286766559;
@@ -336,7 +345,7 @@ __device__ inline int* split_ends(const DecodeArgs& a) {
 }
 
 template <int RMODE, bool PAGED>
-__global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs a, RampOf<RMODE == 2> f) {
   constexpr bool BIFOCAL = RMODE != 0;
   constexpr bool FREQ = RMODE == 2;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kDecSmem];
@@ -441,7 +450,7 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs
   const int fq = BIFOCAL ? remote_pos(qpos, gdiv) : qpos;
   // the frequency map's omega'_i of this lane's frequency (wave 0 forms the
   // step rows, lane i taking frequency i)
-  const double omf_lane = FREQ ? freq_map_omega(a, kv_len, lane) : 0.0;
+  const double omf_lane = FREQ ? freq_map_omega(f, a.w_pre, kv_len, lane) : 0.0;
   const int n_iter = (n_steps + 1) / 2;
 
   // Byte offset of step jb's first key in its cache: a step's 16 keys are
@@ -536,8 +545,8 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs
     for (int i = threadIdx.x; i < kDecTile * 32; i += kDecThreads) {
       const int r = i >> 5, s = i & 31;
       // the frequency map's rows t omega'_i, t = 0..15
-      const float2 cs0 = freq_map_cs(freq_map_omega(a, kv_len, 2 * s), r),
-                   cs1 = freq_map_cs(freq_map_omega(a, kv_len, 2 * s + 1), r);
+      const float2 cs0 = freq_map_cs(freq_map_omega(f, a.w_pre, kv_len, 2 * s), r),
+                   cs1 = freq_map_cs(freq_map_omega(f, a.w_pre, kv_len, 2 * s + 1), r);
       *(float4*)(smem + kDecOffTab2 + r * kDecTabRow + 16 * s) =
           make_float4(cs0.x, cs0.y, cs1.x, cs1.y);
     }
@@ -981,10 +990,11 @@ hipError_t launch_decode(bool bifocal, const uint16_t* q, const uint16_t* kc, co
   if (nwg > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   hipError_t e = hipSuccess;
   const bool freq = bifocal && freq_og != nullptr;
+  FreqRamp ramp;
   if (freq) {
     for (int i = 0; i < kHalf; ++i) {
-      a.fomega[i] = freq_og[i];
-      a.fgamma[i] = freq_og[kHalf + i];
+      ramp.omega[i] = freq_og[i];
+      ramp.gamma[i] = freq_og[kHalf + i];
     }
   }
   // ev0 / ev1 (optional) are recorded on the stream around the split kernel
@@ -992,17 +1002,17 @@ hipError_t launch_decode(bool bifocal, const uint16_t* q, const uint16_t* kc, co
   const dim3 grid((unsigned)nwg), block(kDecThreads);
   const bool paged = block_table != nullptr;
   if (freq && paged)
-    hipLaunchKernelGGL((decode_split_kernel<2, true>), grid, block, 0, stream, a);
+    hipLaunchKernelGGL((decode_split_kernel<2, true>), grid, block, 0, stream, a, ramp);
   else if (freq)
-    hipLaunchKernelGGL((decode_split_kernel<2, false>), grid, block, 0, stream, a);
+    hipLaunchKernelGGL((decode_split_kernel<2, false>), grid, block, 0, stream, a, ramp);
   else if (bifocal && paged)
-    hipLaunchKernelGGL((decode_split_kernel<1, true>), grid, block, 0, stream, a);
+    hipLaunchKernelGGL((decode_split_kernel<1, true>), grid, block, 0, stream, a, NoRamp{});
   else if (bifocal)
-    hipLaunchKernelGGL((decode_split_kernel<1, false>), grid, block, 0, stream, a);
+    hipLaunchKernelGGL((decode_split_kernel<1, false>), grid, block, 0, stream, a, NoRamp{});
   else if (paged)
-    hipLaunchKernelGGL((decode_split_kernel<0, true>), grid, block, 0, stream, a);
+    hipLaunchKernelGGL((decode_split_kernel<0, true>), grid, block, 0, stream, a, NoRamp{});
   else
-    hipLaunchKernelGGL((decode_split_kernel<0, false>), grid, block, 0, stream, a);
+    hipLaunchKernelGGL((decode_split_kernel<0, false>), grid, block, 0, stream, a, NoRamp{});
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (ev1 != nullptr && (e = hipEventRecord(ev1, stream)) != hipSuccess) return e;
   if (B > 1)
