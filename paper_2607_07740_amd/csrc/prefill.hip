@@ -58,8 +58,6 @@ constexpr int kTileBytes = kPfBK * kHeadDim * 2;  // one K tile or one V tile: 1
 // LDS: rotated K tiles (two buffers) and V tiles (two)
 constexpr int kRotOff = 0, kVtOff = 2 * kTileBytes;
 constexpr int kSmemBytes = 4 * kTileBytes;  // 64 KB
-constexpr int kPfCopyBytes = kTileBytes / kPfWaves;  // each wave's share of a tile copy: 8 keys
-constexpr int kKeysPerWave = kPfBK / kPfWaves;
 
 // LDS layouts.
 //   rotated K tile: key r (0..63) at r * 256; its 16-byte
@@ -255,11 +253,13 @@ __device__ inline float* part_state(const PrefillArgs& a, int tail_block, int pa
 // total fell below 2^-slack.  A block with either writes nothing and returns
 // true; the kernel then runs it again with SAFE = true: the per-tile check,
 // which moves the reference as needed.  Every mode runs so.
-template <int MODE, bool SAFE, bool PAGED, bool SPLIT>
+template <int MODE, bool SAFE, bool PAGED, bool SPLIT, int WAVES>
 __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& W,
                                               unsigned char* smem, int* s_bad, int* s_pages,
                                               int part, int parts, float* state) {
   constexpr bool CHECK_LATE = !SAFE;
+  constexpr int kKeys = kPfBK / WAVES;  // each wave's share of a tile: 8 keys, or 16
+  constexpr int kRots = kKeys / 8;
   // The visit list has at most two segments: the fused kernel's remote tiles
   // (segment 1), then tiles [kt_l, n_kt) in one view, keeping 0 <= q - k <= w0
   // (segment 2; w0 = INT_MAX makes it the causal set).
@@ -357,17 +357,19 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
     e.off = (tile_row(e.k0) * a.Hkv + kvh) * kHeadDim;
     return e;
   };
-  // V(j): copy i takes keys 8 wave + 4 i .. + 3 of the tile, lane -> key
+  // V(j): copy i takes keys kKeys wave + 4 i .. + 3 of the tile, lane -> key
   // lane / 16 of them and slot lane % 16, i.e. the chunk that slot holds.
   // Rows past the sequence repeat its last key: their probabilities are zero.
-  const int vrow = 8 * wave + (lane >> 4);
+  const int vrow = kKeys * wave + (lane >> 4);
   const uint32_t vchunk = 16 * ((lane & 15) ^ (4 * (lane >> 4)));
   const uint32_t kv_row_bytes = (uint32_t)a.Hkv * (kHeadDim * 2);  // < 2^24
   auto issue_v = [&](const Ent& e, int jb) __attribute__((always_inline)) {
     const unsigned char* gv = (const unsigned char*)(a.v + e.off);
-    const uint32_t l = smem_base + kVtOff + (jb & 1) * kTileBytes + wave * kPfCopyBytes;
-    dma16_s<0>(gv, __umul24((uint32_t)min(vrow, e.klim), kv_row_bytes) + vchunk, l);
-    dma16_s<0>(gv, __umul24((uint32_t)min(vrow + 4, e.klim), kv_row_bytes) + vchunk, l + 1024);
+    const uint32_t l = smem_base + kVtOff + (jb & 1) * kTileBytes + wave * (kTileBytes / WAVES);
+#pragma unroll
+    for (int i = 0; i < kKeys / 4; ++i)
+      dma16_s<0>(gv, __umul24((uint32_t)min(vrow + 4 * i, e.klim), kv_row_bytes) + vchunk,
+                 l + 1024 * i);
   };
   // Rotation of an entry's raw K tile to its view (Sec. 3.2): lane -> key
   // rt_row of the tile, rotate-half pairs of chunks (rt_c, rt_c + 8), i.e.
@@ -377,14 +379,21 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
   // is one v_dot2_f32_bf16 of the pair (x_i, x_{i+64}) with (cos, -sin) or of
   // (x_{i+64}, x_i) with (cos, sin): exact products, an fp32 sum, then one
   // rounding to bf16.  The result exists only in LDS.
-  const int rt_row = kKeysPerWave * wave + (lane >> 3);
+  // A wave of a 4-wave block does so for two sets of 8 keys.
+  const int rt_row0 = kKeys * wave + (lane >> 3);
   const int rt_c = lane & 7;
-  const int rt_lo = kimg_off(rt_row, rt_c), rt_hi = kimg_off(rt_row, rt_c + 8);
+  int rt_lo[kRots], rt_hi[kRots];
+#pragma unroll
+  for (int h = 0; h < kRots; ++h) {
+    rt_lo[h] = kimg_off(rt_row0 + 8 * h, rt_c);
+    rt_hi[h] = kimg_off(rt_row0 + 8 * h, rt_c + 8);
+  }
   struct RotIn {
     u32x4 xl, xh;  // raw chunks rt_c and rt_c + 8 of key rt_row
     u32x4 ca, cb;  // bf16 (cos, sin) of frequencies 8 rt_c .. +3 and +4 .. +7
   };
-  auto rot_load = [&](const Ent& e) __attribute__((always_inline)) {
+  auto rot_load1 = [&](const Ent& e, int h) __attribute__((always_inline)) {
+    const int rt_row = rt_row0 + 8 * h;
     int fr = (int)fastdiv_ge2((uint32_t)(e.kmod + rt_row), gdiv);
     asm volatile("" : "+v"(fr));  // formed unconditionally: a select, not a branch
     const int row = min(e.alias ? fr : rt_row, e.tlim);
@@ -409,16 +418,25 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
     lo[w] = l;
     hi[w] = h;
   };
-  auto rot_store = [&](int jb, const u32x4& lo, const u32x4& hi) __attribute__((always_inline)) {
-    unsigned char* dst = smem + kRotOff + (jb & 1) * kTileBytes;
-    *(u32x4*)(dst + rt_lo) = lo;
-    *(u32x4*)(dst + rt_hi) = hi;
+  struct RotSet {
+    RotIn r[kRots];
   };
-  auto rotate = [&](const RotIn& r, int jb) __attribute__((always_inline)) {
-    u32x4 lo, hi;
+  auto rot_load = [&](const Ent& e) __attribute__((always_inline)) {
+    RotSet s;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) rot_word(r, w, lo, hi);
-    rot_store(jb, lo, hi);
+    for (int h = 0; h < kRots; ++h) s.r[h] = rot_load1(e, h);
+    return s;
+  };
+  auto rotate = [&](const RotSet& s, int jb) __attribute__((always_inline)) {
+    unsigned char* dst = smem + kRotOff + (jb & 1) * kTileBytes;
+#pragma unroll
+    for (int h = 0; h < kRots; ++h) {
+      u32x4 lo, hi;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) rot_word(s.r[h], w, lo, hi);
+      *(u32x4*)(dst + rt_lo[h]) = lo;
+      *(u32x4*)(dst + rt_hi[h]) = hi;
+    }
   };
   auto kbuf = [&](int j) __attribute__((always_inline)) {
     return (const unsigned char*)smem + kRotOff + (j & 1) * kTileBytes;
@@ -621,7 +639,7 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
 #pragma unroll
       for (int m = 0; m < 4; ++m) ring[m] = kop(m);
       __builtin_amdgcn_sched_barrier(0);
-      RotIn rin;
+      RotSet rin;
 #pragma unroll
       for (int m = 0; m < 16; ++m) {
         const int blk = m & 1, st = m >> 1;
@@ -687,7 +705,7 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
       float ps = softmax(cur, pb);
       ref_fix(cur, nxt, pb, ps);
       l_run += ps;
-      const RotIn rin = rot_load(pend);  // loaded late: short-lived registers
+      const RotSet rin = rot_load(pend);  // loaded late: short-lived registers
       pv(vbuf(j), pb);
       rotate(rin, j + 2);
       vent = pend;
@@ -712,7 +730,7 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
   const int last = n_steps - 1;
   if constexpr (PAGED) {  // the sequence's page list, clamped into the pool
     const int np = min((Lk + (1 << a.page_shift) - 1) >> a.page_shift, kMaxSeqPages);
-    for (int i = tid; i < np; i += kPfThreads) {
+    for (int i = tid; i < np; i += 64 * WAVES) {
       const int pg = a.block_table[(size_t)W.b * a.max_pages + i];
       s_pages[i] = pg < 0 ? 0 : (pg >= a.n_pages ? a.n_pages - 1 : pg);
     }
@@ -721,7 +739,7 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
   Ent pend = ent_of(0), vent = ent_of(min(1, last));
   {
     issue_v(pend, 0);
-    const RotIn r0 = rot_load(pend), r1 = rot_load(vent);
+    const RotSet r0 = rot_load(pend), r1 = rot_load(vent);
     rotate(r0, 0);
     rotate(r1, 1);
   }
@@ -795,8 +813,8 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
   return false;
 }
 
-template <int MODE, bool PAGED = false, bool SPLIT = false>
-__global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
+template <int MODE, bool PAGED = false, bool SPLIT = false, int WAVES = kPfWaves>
+__global__ __launch_bounds__(64 * WAVES, WAVES == kPfWaves ? 2 : 1) void prefill_kernel(PrefillArgs a) {
   // LDS: rotated K tiles and V tiles, two buffers each
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kSmemBytes];
   __shared__ int s_bad;
@@ -815,9 +833,9 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_kernel(PrefillArgs a) {
     if (part >= parts) return;
     state = part_state(a, bid - a.n_whole, part);
   }
-  if (prefill_block<MODE, false, PAGED, SPLIT>(a, W, smem, &s_bad, s_pages, part, parts, state)) {
+  if (prefill_block<MODE, false, PAGED, SPLIT, WAVES>(a, W, smem, &s_bad, s_pages, part, parts, state)) {
     __syncthreads();  // every wave is done with the fast pass's tiles
-    prefill_block<MODE, true, PAGED, SPLIT>(a, W, smem, &s_bad, s_pages, part, parts, state);
+    prefill_block<MODE, true, PAGED, SPLIT, WAVES>(a, W, smem, &s_bad, s_pages, part, parts, state);
   }
 }
 
@@ -961,9 +979,9 @@ static void fill_geometry(PrefillArgs& a, int B, int Hq, int Hkv, int L, int q_s
   a.slack = slack;
 }
 
-template <int MODE, bool PAGED = false>
+template <int MODE, bool PAGED = false, int WAVES = kPfWaves>
 static hipError_t launch_blocks(const PrefillArgs& a, dim3 grid, hipStream_t stream) {
-  hipLaunchKernelGGL((prefill_kernel<MODE, PAGED>), grid, dim3(kPfThreads), 0, stream, a);
+  hipLaunchKernelGGL((prefill_kernel<MODE, PAGED, false, WAVES>), grid, dim3(64 * WAVES), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -1020,6 +1038,14 @@ static PrefillSplit prefill_split(int n_cu, long long n_blocks, int q_start, int
     }
   }
   return best;
+}
+
+// A call of at most half as many blocks as CUs whose blocks are not cut runs
+// blocks of half the rows on 4 waves instead: one wave per SIMD, half the work
+// per CU and visit.
+constexpr int kPfHalfWaves = kPfWaves / 2;
+static bool half_blocks(int n_cu, const PrefillArgs& a) {
+  return 2LL * a.n_blocks <= n_cu && a.BQ >= 2;
 }
 
 // Bytes of scratch a call needs for the states of its parts (0: no block is cut)
@@ -1084,6 +1110,16 @@ hipError_t launch_prefill_chunk(bool bifocal, const uint16_t* q, const uint16_t*
                          : launch_split_blocks<kModeFused, false>(a, stream))
                 : (paged ? launch_split_blocks<kModeVanilla, true>(a, stream)
                          : launch_split_blocks<kModeVanilla, false>(a, stream));
+  } else if (half_blocks(n_cu, a)) {
+    a.BQ /= 2;
+    a.n_qblocks = (Lq + a.BQ - 1) / a.BQ;
+    a.n_blocks = a.n_qblocks * B * Hkv;
+    const dim3 grid((unsigned)a.n_blocks);
+    const bool paged = block_table != nullptr;
+    e = bifocal ? (paged ? launch_blocks<kModeFused, true, kPfHalfWaves>(a, grid, stream)
+                         : launch_blocks<kModeFused, false, kPfHalfWaves>(a, grid, stream))
+                : (paged ? launch_blocks<kModeVanilla, true, kPfHalfWaves>(a, grid, stream)
+                         : launch_blocks<kModeVanilla, false, kPfHalfWaves>(a, grid, stream));
   } else {
     e = launch_attn(bifocal ? kModeFused : kModeVanilla, a, stream);
   }
