@@ -31,8 +31,9 @@
  *      - the RoPE cos/sin table (per device and rope_theta, grown by
  *        doubling to cover the call's positions): every prefill and decode
  *        entry point; growing allocates and waits for `stream`;
- *      - the prefill scratch (per device and stream): the _varlen forms, and
- *        of jl_bifocal_prefill, jl_rope_attention, their _map and _chunk forms
+ *      - the prefill scratch (per device and stream): the _varlen forms with
+ *        more than 64 sequences or the frequency map, and of
+ *        jl_bifocal_prefill, jl_rope_attention, their _map and _chunk forms
  *        the calls whose query blocks leave CUs idle (see there); growing
  *        waits for `stream`, frees the old buffer and allocates;
  *      - the frequency-map table (one per device): jl_bifocal_prefill_map
@@ -201,7 +202,7 @@ int jl_rope_attention_chunk_paged(const void* q, const void* k_pages, const void
 /*
  * Packed (variable-length) bifocal prefill: B independent sequences of
  * different lengths in one call, each computed exactly as jl_bifocal_prefill
- * would compute it alone -- its own L, G = max(1, ceil(L / w_pretrained))
+ * would compute it alone (but for that call's cut blocks) -- its own L, G = max(1, ceil(L / w_pretrained))
  * (Eq. (2)), positions 0 .. L - 1, Eq. (3) remote positions and the Eq. (7)
  * bifocal result (a sequence with G = 1 gets the base model, as there).
  *   q, o: bf16 [total_tokens, Hq, head_dim]; k, v: bf16 [total_tokens, Hkv,
@@ -216,8 +217,8 @@ int jl_rope_attention_chunk_paged(const void* q, const void* k_pages, const void
  * clamped into [0, total_tokens] (a decreasing step gives an empty sequence)
  * and a sequence whose work would not fit the lists sized for well-formed
  * input is skipped; output rows of skipped, cut or uncovered positions are
- * left as they were.  Scratch (the library's, per stream): a work list of 16
- * bytes per query block.  Other requirements and errors as in jl_bifocal_prefill; only the Eq. (3) map.
+ * left as they were.  Scratch (the library's, per stream): none up to 64
+ * sequences, beyond that a work list of 16 bytes per query block.  Other requirements and errors as in jl_bifocal_prefill; only the Eq. (3) map.
  */
 int jl_bifocal_prefill_varlen(const void* q, const void* k, const void* v, void* o, float* lse,
                               const int32_t* cu_seqlens, int B, int total_tokens, int max_seqlen,
@@ -230,7 +231,7 @@ int jl_bifocal_prefill_varlen(const void* q, const void* k, const void* v, void*
  * jl_bifocal_prefill_varlen bit for bit; JL_REMOTE_FREQ gives every sequence
  * the frequency map of its own length: factor s = max(1, L / w_pretrained),
  * positions unchanged, each sequence equal bit for bit to jl_bifocal_prefill_map
- * on that sequence alone.  The per-sequence tables (768 bytes per token) are
+ * on that sequence alone (where that call cuts no block, see jl_bifocal_prefill).  The per-sequence tables (768 bytes per token) are
  * built on the device into the library scratch.  Other arguments and errors
  * as in jl_bifocal_prefill_varlen; remote_map outside {0, 1} ->
  * JL_ERR_INVALID_ARG.

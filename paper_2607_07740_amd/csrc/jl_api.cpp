@@ -34,8 +34,9 @@ hipError_t launch_prefill_varlen(bool bifocal, const uint16_t* q, const uint16_t
                                  const uint16_t* v, uint16_t* o, float* lse, const float2* table,
                                  const uint32_t* table16, const int32_t* cu, int B, int T,
                                  int max_len, int Hq, int Hkv,
-                                 int w_pre, int w0, float slack, void* ws, hipStream_t stream,
-                                 hipEvent_t ev0, hipEvent_t ev1, const double* freq_og);
+                                 int w_pre, int w0, float slack, int n_cu, void* ws,
+                                 hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1,
+                                 const double* freq_og);
 size_t literal_workspace_bytes(int B, int Hq, int Hkv, int L);
 hipError_t launch_prefill_literal(const uint16_t* q, const uint16_t* k, const uint16_t* v,
                                   uint16_t* o, float* lse, const float2* table,
@@ -466,10 +467,14 @@ int prefill_varlen(bool bifocal, const void* q, const void* k, const void* v, vo
   st = get_table(theta, max_len, s, &tab);
   if (st != JL_OK) return st;
   const float slack = (float)g_rescale_log2.load();
-  std::lock_guard<std::mutex> launch_lock(g_prefill_mu);
   void* scratch = nullptr;
-  st = get_scratch(s, jl::prefill_varlen_workspace_bytes(B, T, Hq, Hkv, freq), &scratch);
-  if (st != JL_OK) return st;
+  std::unique_lock<std::mutex> launch_lock(g_prefill_mu, std::defer_lock);
+  const size_t scratch_bytes = jl::prefill_varlen_workspace_bytes(B, T, Hq, Hkv, freq);
+  if (scratch_bytes > 0) {
+    launch_lock.lock();
+    st = get_scratch(s, scratch_bytes, &scratch);
+    if (st != JL_OK) return st;
+  }
   double og[128];
   if (freq) freq_map_ramp(theta, w_pre, og);
   hipEvent_t ev0, ev1;
@@ -477,8 +482,8 @@ int prefill_varlen(bool bifocal, const void* q, const void* k, const void* v, vo
   hipError_t e = jl::launch_prefill_varlen(bifocal, (const uint16_t*)q, (const uint16_t*)k,
                                            (const uint16_t*)v, (uint16_t*)o, lse, tab.f32, tab.f16,
                                            cu, B, T,
-                                           max_len, Hq, Hkv, w_pre, w0, slack, scratch, s, ev0,
-                                           ev1, freq ? og : nullptr);
+                                           max_len, Hq, Hkv, w_pre, w0, slack, jl::cu_count(),
+                                           scratch, s, ev0, ev1, freq ? og : nullptr);
   if (e != hipSuccess) return hip_fail(e, "varlen prefill launch");
   return ok();
 }

@@ -108,6 +108,11 @@ struct PrefillArgs {
   // G = group_size(L, w_pre)
   const int4* qwork;
   int w_pre;
+  // or, for at most kPlanLanes sequences, the offsets themselves: each
+  // workgroup forms its entry (plan_entry).  nq, nt: the lists' sizes for
+  // blocks of plan_BQ queries, which decide which sequences of a malformed cu run
+  const int32_t* cu;
+  int n_seq, plan_BQ, nq, nt;
   // paged caches (nullptr otherwise): k and v are pools [n_pages][page][Hkv][128],
   // pages of at least 64 keys, so a tile lies in one page
   const int32_t* block_table;
@@ -134,16 +139,53 @@ struct Work {
   FastDiv gdiv;
 };
 
+// Entry `item` of a packed batch's query-block list, (seq0, L, q block, 0) as
+// varlen_plan_kernel writes it, formed by every wave of the workgroup from the
+// offsets: lane = sequence, a wave scan of the block counts, and the first
+// sequence whose inclusive count exceeds the item owns it.  Counts saturate:
+// sequences of a malformed cu may overlap.
+constexpr int kPlanLanes = 64;
+__device__ inline int4 plan_entry(const PrefillArgs& a, int item) {
+  const int lane = threadIdx.x & 63;
+  int seq0 = 0, len = 0;
+  if (lane < a.n_seq) {
+    seq0 = min(max(a.cu[lane], 0), a.Lq);
+    const int seq1 = min(max(a.cu[lane + 1], seq0), a.Lq);
+    len = min(seq1 - seq0, a.L);
+  }
+  // block sizes are powers of two: Hq / Hkv divides the rows of a block
+  const uint32_t last = (uint32_t)(len - 1);
+  const uint32_t nb = len > 0 ? (last >> __builtin_ctz(a.BQ)) + 1 : 0;
+  uint32_t inc = nb, inc_q = len > 0 ? (last >> __builtin_ctz(a.plan_BQ)) + 1 : 0;
+  uint32_t inc_t = len > 0 ? last / kPfBK + 1 : 0;
+#pragma unroll
+  for (int d = 1; d < kPlanLanes; d <<= 1) {
+    const uint32_t x = __shfl_up(inc, d), xq = __shfl_up(inc_q, d), xt = __shfl_up(inc_t, d);
+    if (lane >= d) {
+      inc = min(inc + x, 0x7fffffffu);
+      inc_q = min(inc_q + xq, 0x7fffffffu);
+      inc_t = min(inc_t + xt, 0x7fffffffu);
+    }
+  }
+  const unsigned long long past = __ballot(inc > (uint32_t)item);
+  if (past == 0) return int4{0, 0, 0, 0};
+  const int j = __builtin_ctzll(past);
+  const bool fits = inc_q <= (uint32_t)a.nq && inc_t <= (uint32_t)a.nt;
+  const int run = __builtin_amdgcn_readlane(fits ? len : 0, j);
+  return int4{__builtin_amdgcn_readlane(seq0, j), run,
+              __builtin_amdgcn_readlane((int)inc, j) - 1 - item, 0};
+}
+
 // false: no query block here (an unused entry of a packed batch's plan)
 __device__ inline bool work_of(const PrefillArgs& a, int bid, bool fused, Work& W) {
   const int n_groups = a.B * a.Hkv;
-  if (a.qwork != nullptr) {
+  if (a.qwork != nullptr || a.cu != nullptr) {
     // packed batch: the work item's sequence, its G, its tiles; the kv head
     // follows the XCD (bid & 7) when Hkv divides 8
     const int item = bid / a.Hkv;
     W.b = 0;
     W.kvh = bid - item * a.Hkv;
-    const int4 w = a.qwork[item];
+    const int4 w = a.cu != nullptr ? plan_entry(a, item) : a.qwork[item];
     if (w.y <= 0) return false;
     const int G = fused ? group_size(w.y, a.w_pre) : 1;
     W.gdiv = make_fastdiv((uint32_t)G);
@@ -1257,7 +1299,7 @@ static void varlen_sizes(int B, int T, int g, long long* nq, long long* nt) {
   *nt = ((long long)T + kPfBK - 1) / kPfBK + B;
 }
 
-// Scratch of a packed call: the query-block work list, then (frequency map
+// Scratch of a packed call with a planning kernel: the query-block work list, then (frequency map
 // only) the tile list and the per-sequence remote tables, fp32 and bf16, one
 // row per token.
 static size_t varlen_lists_end(int B, int T, int Hq, int Hkv, bool freq) {
@@ -1266,7 +1308,15 @@ static size_t varlen_lists_end(int B, int T, int Hq, int Hkv, bool freq) {
   return (size_t)(nq + (freq ? nt : 0)) * sizeof(int4);
 }
 
+// Whether the attention kernel forms its work entries itself.  The frequency
+// map's tables are built from the tile list, and more sequences than lanes
+// would take a loop of scans in every workgroup.  Planning kernel -> own
+// entries, us per call: 4 x 250 tokens, 16/8 heads, 25.8 -> 20.8; 8 x 64, 32/8,
+// 20.7 -> 16.0; 60 x 5, 16/8, 21.1 -> 16.5; 2000 + 500 + 300, 32/8, 72.8 -> 65.5.
+static bool varlen_planless(int B, bool freq) { return B <= kPlanLanes && !freq; }
+
 size_t prefill_varlen_workspace_bytes(int B, int T, int Hq, int Hkv, bool freq) {
+  if (varlen_planless(B, freq)) return 0;
   const size_t base = varlen_lists_end(B, T, Hq, Hkv, freq);
   if (!freq) return base;
   return round256(base) + (size_t)T * kHalf * (sizeof(float2) + sizeof(uint32_t));
@@ -1282,8 +1332,9 @@ hipError_t launch_prefill_varlen(bool bifocal, const uint16_t* q, const uint16_t
                                  const uint16_t* v, uint16_t* o, float* lse, const float2* table,
                                  const uint32_t* table16, const int32_t* cu, int B, int T,
                                  int max_len, int Hq, int Hkv,
-                                 int w_pre, int w0, float slack, void* ws, hipStream_t stream,
-                                 hipEvent_t ev0, hipEvent_t ev1, const double* freq_og) {
+                                 int w_pre, int w0, float slack, int n_cu, void* ws,
+                                 hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1,
+                                 const double* freq_og) {
   long long nq, nt;
   varlen_sizes(B, T, Hq / Hkv, &nq, &nt);
   if (nq * Hkv > 0x7fffffffLL || nt > 0x7fffffffLL || Hkv > 65535)
@@ -1292,13 +1343,27 @@ hipError_t launch_prefill_varlen(bool bifocal, const uint16_t* q, const uint16_t
   PrefillArgs a = {};
   fill_geometry(a, 1, Hq, Hkv, max_len, 0, T, slack);
   fill_inputs(a, q, k, v, table, table, table16, table16, 0, T, 1);
-  int4* qwork = (int4*)ws;
-  int4* twork = freq ? qwork + nq : nullptr;
   a.o = o;
   a.lse = lse;
   a.w0 = bifocal ? w0 : INT_MAX;
-  a.qwork = qwork;
   a.w_pre = w_pre;
+  if (varlen_planless(B, freq)) {
+    a.cu = cu;
+    a.n_seq = B;
+    a.plan_BQ = a.BQ;
+    a.nq = (int)nq;
+    a.nt = (int)nt;
+    hipError_t e = hipSuccess;
+    if (ev0 != nullptr && (e = hipEventRecord(ev0, stream)) != hipSuccess) return e;
+    const dim3 grid((unsigned)(nq * Hkv));
+    e = bifocal ? launch_blocks<kModeFused>(a, grid, stream)
+                : launch_blocks<kModeVanilla>(a, grid, stream);
+    if (e == hipSuccess && ev1 != nullptr) e = hipEventRecord(ev1, stream);
+    return e;
+  }
+  int4* qwork = (int4*)ws;
+  int4* twork = freq ? qwork + nq : nullptr;
+  a.qwork = qwork;
 
   PlanArgs pl;
   pl.cu = cu;

@@ -194,3 +194,28 @@ def test_varlen_freq_map_per_sequence(g):
         want, _ = O.prefill(q[None, a:b], k[None, a:b], v[None, a:b], theta=1e6, w_pretrained=w,
                             w_local=w0, remote_map="freq")
         assert_close(o[a:b], want[0], what="freq seq %d L=%d" % (s, L))
+
+
+@pytest.mark.parametrize("g,w,lens", [
+    (2, 100, [1]),
+    (4, 100, [300]),
+    (1, 4096, [0, 0, 257, 0]),
+    (8, 64, [5, 0, 64, 65] * 16),           # 64 sequences: every lane of the scan
+    (4, 300, [0] * 63 + [700]),             # only the last lane has a sequence
+    (2, 512, [2100, 900, 1, 1300, 0, 31]),  # lists of both segments of the visit order
+])
+def test_varlen_entries_without_planning_kernel(g, w, lens):
+    """Up to 64 sequences each workgroup finds its own block; beyond, a planning
+    kernel lists them.  The same batch with empty sequences appended up to 70
+    takes the second way: same bits, NaN left where no sequence lies."""
+    Hkv, w0 = 2, 30
+    q, k, v, cu = _pack(lens + [9], g * Hkv, Hkv, seed=sum(lens) + g)  # 9 uncovered rows
+    cu = cu[:-1]
+    padded = np.concatenate([cu, np.full(70 - len(lens), cu[-1], dtype=np.int32)])
+    for bifocal in (True, False):
+        say("varlen entries g=%d B=%d bifocal=%s" % (g, len(lens), bifocal))
+        a, la = _varlen(q, k, v, cu, max(lens), bifocal, w, w0)
+        b, lb = _varlen(q, k, v, padded, max(lens), bifocal, w, w0)
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+        assert torch.equal(la.view(torch.int32), lb.view(torch.int32))
+        assert torch.isfinite(a[:cu[-1]].float()).all() and torch.isnan(a[cu[-1]:].float()).all()
