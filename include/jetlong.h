@@ -202,9 +202,10 @@ int jl_rope_attention_chunk_paged(const void* q, const void* k_pages, const void
 /*
  * Packed (variable-length) bifocal prefill: B independent sequences of
  * different lengths in one call, each computed exactly as jl_bifocal_prefill
- * would compute it alone (but for that call's cut blocks) -- its own L, G = max(1, ceil(L / w_pretrained))
- * (Eq. (2)), positions 0 .. L - 1, Eq. (3) remote positions and the Eq. (7)
- * bifocal result (a sequence with G = 1 gets the base model, as there).
+ * would compute it alone (where that call cuts no block) -- its own L,
+ * G = max(1, ceil(L / w_pretrained)) (Eq. (2)), positions 0 .. L - 1, Eq. (3)
+ * remote positions and the Eq. (7) bifocal result (a sequence with G = 1 gets
+ * the base model, as there).
  *   q, o: bf16 [total_tokens, Hq, head_dim]; k, v: bf16 [total_tokens, Hkv,
  *     head_dim] (raw, before RoPE); sequence s holds rows
  *     cu_seqlens[s] .. cu_seqlens[s + 1] - 1.
@@ -218,7 +219,8 @@ int jl_rope_attention_chunk_paged(const void* q, const void* k_pages, const void
  * and a sequence whose work would not fit the lists sized for well-formed
  * input is skipped; output rows of skipped, cut or uncovered positions are
  * left as they were.  Scratch (the library's, per stream): none up to 64
- * sequences, beyond that a work list of 16 bytes per query block.  Other requirements and errors as in jl_bifocal_prefill; only the Eq. (3) map.
+ * sequences, beyond that a work list of 16 bytes per query block.  Other
+ * requirements and errors as in jl_bifocal_prefill; only the Eq. (3) map.
  */
 int jl_bifocal_prefill_varlen(const void* q, const void* k, const void* v, void* o, float* lse,
                               const int32_t* cu_seqlens, int B, int total_tokens, int max_seqlen,
@@ -231,7 +233,8 @@ int jl_bifocal_prefill_varlen(const void* q, const void* k, const void* v, void*
  * jl_bifocal_prefill_varlen bit for bit; JL_REMOTE_FREQ gives every sequence
  * the frequency map of its own length: factor s = max(1, L / w_pretrained),
  * positions unchanged, each sequence equal bit for bit to jl_bifocal_prefill_map
- * on that sequence alone (where that call cuts no block, see jl_bifocal_prefill).  The per-sequence tables (768 bytes per token) are
+ * on that sequence alone (where that call cuts no block, see
+ * jl_bifocal_prefill).  The per-sequence tables (768 bytes per token) are
  * built on the device into the library scratch.  Other arguments and errors
  * as in jl_bifocal_prefill_varlen; remote_map outside {0, 1} ->
  * JL_ERR_INVALID_ARG.

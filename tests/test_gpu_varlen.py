@@ -219,3 +219,28 @@ def test_varlen_entries_without_planning_kernel(g, w, lens):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
         assert torch.equal(la.view(torch.int32), lb.view(torch.int32))
         assert torch.isfinite(a[:cu[-1]].float()).all() and torch.isnan(a[cu[-1]:].float()).all()
+
+
+@pytest.mark.parametrize("Hq,Hkv,L", [
+    (2, 1, 1), (16, 8, 1000), (16, 8, 2048), (16, 8, 2049), (8, 8, 129),
+    (128, 1, 70), (256, 1, 40),  # blocks of 2 positions, halved; of 1, which cannot be
+])
+def test_half_blocks_equal_whole_blocks(Hq, Hkv, L):
+    """A call of at most half as many blocks as CUs runs blocks of half the rows
+    (2048 tokens of 16/8 heads are 128 blocks, one token more is 136): dense and
+    packed, the bits of the packed call with empty sequences appended up to 70,
+    which runs whole blocks."""
+    w, w0 = 300, 70
+    q, k, v, cu = _pack([L], Hq, Hkv, seed=L + Hq)
+    whole = np.concatenate([cu, np.full(69, L, dtype=np.int32)])
+    for bifocal in (True, False):
+        say("half blocks %d/%d L=%d bifocal=%s" % (Hq, Hkv, L, bifocal))
+        a, la = _varlen(q, k, v, whole, L, bifocal, w, w0)
+        b, lb = _varlen(q, k, v, cu, L, bifocal, w, w0)
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+        assert torch.equal(la.view(torch.int32), lb.view(torch.int32))
+        d, ld = api._prefill(bifocal, to_dev(q[None]), to_dev(k[None]), to_dev(v[None]), w, w0,
+                             1e6, None, None, True, None)
+        torch.cuda.synchronize()
+        assert torch.equal(a.view(torch.int16), d[0].view(torch.int16))
+        assert torch.equal(la.view(torch.int32), ld[0].view(torch.int32))
