@@ -32,7 +32,7 @@
  *        doubling to cover the call's positions): every prefill and decode
  *        entry point; growing allocates and waits for `stream`;
  *      - the prefill scratch (per device and stream): the _varlen forms with
- *        more than 64 sequences or the frequency map, and of
+ *        more than 64 sequences, or the frequency map past the window, and of
  *        jl_bifocal_prefill, jl_rope_attention, their _map and _chunk forms
  *        the calls whose query blocks leave CUs idle (see there); growing
  *        waits for `stream`, frees the old buffer and allocates;

@@ -244,3 +244,28 @@ def test_half_blocks_equal_whole_blocks(Hq, Hkv, L):
         torch.cuda.synchronize()
         assert torch.equal(a.view(torch.int16), d[0].view(torch.int16))
         assert torch.equal(la.view(torch.int32), ld[0].view(torch.int32))
+
+
+@pytest.mark.parametrize("remote_map", ["alias", "freq"])
+@pytest.mark.parametrize("w,max_seqlen", [(300, 300), (299, 300), (300, 5000)])
+def test_varlen_within_window(remote_map, w, max_seqlen):
+    """Batches whose max_seqlen lies within the window run the vanilla kernel;
+    with a larger bound, or a window one shorter, the fused one.  The sequences
+    with G = 1 get the vanilla call's bits either way."""
+    Hq, Hkv, lens = 8, 2, [300, 41, 0, 128, 299]
+    q, k, v, cu = _pack(lens + [5000 - sum(lens)], Hq, Hkv, seed=w)
+    q, k, v, cu = q[:cu[-2]], k[:cu[-2]], v[:cu[-2]], cu[:-1]
+    if max_seqlen > cu[-1]:  # the bound must exceed the window after its cut to the token count
+        assert cu[-1] > w
+    say("varlen within window w=%d max=%d %s" % (w, max_seqlen, remote_map))
+    qd = to_dev(q)
+    out = torch.full_like(qd, float("nan"))
+    api.prefill_varlen(qd, to_dev(k), to_dev(v), torch.from_numpy(cu).cuda(),
+                       max_seqlen=max_seqlen, w_pretrained=w, w_local=20, out=out,
+                       remote_map=remote_map)
+    torch.cuda.synchronize()
+    van, _ = _varlen(q, k, v, cu, max_seqlen, False, w, 20)
+    for s, L in enumerate(lens):
+        if L <= w:
+            a, b = cu[s], cu[s + 1]
+            assert torch.equal(out[a:b].view(torch.int16), van[a:b].view(torch.int16)), s
