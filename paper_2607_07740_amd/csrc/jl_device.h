@@ -199,24 +199,31 @@ __device__ inline uint32_t lds_addr(const void* p) {
 // counter alone: call wait_vmem() before the bytes are read.  Inline assembly
 // keeps the compiler from adding a conservative wait in front of every LDS
 // read that follows the copy.
-// The compiler loads M0 itself (operand constraint); the s_nop is the wait
-// state an LDS-bound load needs after an M0 write.
 // The base is wave-uniform and 64-bit, in scalar registers, with a 32-bit
 // per-lane byte offset; imm is added to both the global and the LDS address.
+// The compiler loads M0 itself (operand constraint), but does not look inside
+// the block for the wait states the load needs, so the block keeps them: one
+// after the M0 write, and five after a VALU write of the base, which is what
+// a reload of a spilled scalar register is (v_readlane).  A load too soon after
+// one takes a stale base and may fault.  The scalar move serves both: it is
+// that one wait state, scalar instructions wait for VALU results by
+// themselves, and a load may read what one of them wrote at once.  Its target
+// is VCC, which costs the kernels no register (a pair of its own: 10 more
+// spilled ones in the decode kernels).
 template <int imm = 0>
 __device__ inline void dma16_s(const void* sbase, uint32_t voff, uint32_t lds_base) {
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%2"
+  asm volatile("s_mov_b64 vcc, %1\n\tglobal_load_lds_dwordx4 %0, vcc offset:%2"
                :
                : "v"(voff), "s"(sbase), "i"(imm), "{m0}"(lds_base)
-               : "memory");
+               : "memory", "vcc");
 }
 // The same copy with the nontemporal hint, for data that is read exactly once.
 template <int imm = 0>
 __device__ inline void dma16_s_nt(const void* sbase, uint32_t voff, uint32_t lds_base) {
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%2 nt"
+  asm volatile("s_mov_b64 vcc, %1\n\tglobal_load_lds_dwordx4 %0, vcc offset:%2 nt"
                :
                : "v"(voff), "s"(sbase), "i"(imm), "{m0}"(lds_base)
-               : "memory");
+               : "memory", "vcc");
 }
 __device__ inline void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // Wait until at most N of this wave's vector-memory operations are in flight

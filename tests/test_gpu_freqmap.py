@@ -157,3 +157,32 @@ def test_freq_map_decode_alias_entry_equals_plain_decode():
                            w_pretrained=w_pre, w_local=w0)
     torch.cuda.synchronize()
     assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("g,n,w_pre", [(8, 8878, 32768), (4, 5003, 1024)])
+def test_freq_map_paged_decode_of_one_long_sequence(g, n, w_pre):
+    """A sequence of several steps per workgroup on a paged cache, under the
+    frequency map: the copies' base addresses are scalar registers that this
+    kernel keeps spilled between them.  Against the dense cache's bits and the
+    oracle."""
+    Hkv, page, w0 = 8, 256, 300
+    pages = -(-n // page)
+    q, kc, vc, lens = synth.decode_inputs(1, g * Hkv, Hkv, pages * page, [n], seed=n, nan_tail=True)
+    say("freq-map paged decode n=%d g=%d" % (n, g))
+    order = torch.from_numpy(np.random.default_rng(n).permutation(pages))
+    pool_k, pool_v = (torch.empty((pages, page, Hkv, 128), dtype=torch.bfloat16, device="cuda")
+                      for _ in range(2))
+    pool_k[order.cuda()] = to_dev(kc).view(pages, page, Hkv, 128)
+    pool_v[order.cuda()] = to_dev(vc).view(pages, page, Hkv, 128)
+    table = order.to(torch.int32).view(1, pages).cuda()
+    ld = torch.from_numpy(lens).cuda()
+    torch.cuda.synchronize()
+    dense = _decode_freq(q, kc, vc, lens, w_pre, w0)
+    for _ in range(3):
+        out = api.decode_paged(to_dev(q), pool_k, pool_v, table, ld, w_pretrained=w_pre, w_local=w0,
+                               remote_map="freq")
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), dense.view(torch.int16))
+    want, _, _ = O.decode(q, kc, vc, lens, theta=1e6, w_pretrained=w_pre, w_local=w0,
+                          remote_map="freq")
+    assert_close(to_f64(out), want, what="freq paged decode n=%d" % n)
