@@ -810,12 +810,11 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
 
   // ---- normalise and write
   const float l_tot = l_run + __shfl_xor(l_run, 32);
-  if (CHECK_LATE) {
-    late_bad |= __ballot(row_valid && !(l_tot >= p_lo));
-    if (late_bad != 0 && lane == 0) *s_bad = 1;
-    __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(*s_bad) != 0) return true;
-  }
+  // A part's state goes out ahead of the check, whatever it finds: the checked
+  // pass writes it again.  Behind the check the store was placed after the
+  // checked pass, which then ran with the fast pass's 64 accumulators live and
+  // spilled its own operands: 3000 queries behind 40000 keys, 32/8 heads, whose
+  // scores trip the check, took 5950 us (3825 now; 4758 as whole blocks).
   if (SPLIT && parts > 1) {  // rows past the last query repeat it: their states are not read
     asm volatile("" : "+s"(state));  // or the addresses are formed, and kept, before the loops
     const uint32_t lane4 = (uint32_t)(hl32 * kPfRows + row);
@@ -830,8 +829,14 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
       }
     }
     if (hl32 == 0) ((float2*)(state + kPfRows * kHeadDim))[row] = make_float2(m_ref, l_tot);
-    return false;
   }
+  if (CHECK_LATE) {
+    late_bad |= __ballot(row_valid && !(l_tot >= p_lo));
+    if (late_bad != 0 && lane == 0) *s_bad = 1;
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(*s_bad) != 0) return true;
+  }
+  if (SPLIT && parts > 1) return false;
   if (row_valid) {
     const float inv = 1.f / l_tot;
     const size_t orow_off = ((row_base + qr) * a.Hq + hd) * kHeadDim;
