@@ -298,8 +298,13 @@ int jl_bifocal_prefill_literal(const void* q, const void* k, const void* v, void
                                size_t workspace_bytes, void* stream);
 
 /*
- * Bytes of device workspace the decode entry points need for this shape
+ * Bytes of device workspace the decode entry points use for this shape
  * (split-K partial softmax states).  Returns 0 for invalid arguments.
+ * A smaller workspace is accepted down to B * Hq * n * 528 bytes with n =
+ * min(128, ceil(max_len / 16)) up to B = 64 and n = min(ceil(256 / (B *
+ * ceil(Hkv / 4))), 128, ceil(max_len / 16)) beyond: the call then runs fewer
+ * workgroups, or the batch in parts one after another, and its results equal
+ * those with the full workspace up to the splits of the softmax sums.
  */
 size_t jl_decode_workspace_bytes(int B, int Hq, int Hkv, int max_len, int head_dim);
 
@@ -317,9 +322,10 @@ size_t jl_decode_workspace_bytes(int B, int Hq, int Hkv, int max_len, int head_d
  *            max_len, so a bad length gives wrong values, never an
  *            out-of-bounds read
  *   o        bf16 [B, Hq, head_dim] output (written)
- *   workspace, workspace_bytes: device scratch of at least
- *            jl_decode_workspace_bytes(B, Hq, Hkv, max_len, head_dim) bytes,
- *            16-byte aligned; its contents on entry do not matter.
+ *   workspace, workspace_bytes: device scratch of
+ *            jl_decode_workspace_bytes(B, Hq, Hkv, max_len, head_dim) bytes
+ *            (or somewhat less, see there), 16-byte aligned; its contents on
+ *            entry do not matter.
  * G is taken per sequence from L = kv_lens[b] on the device, so one cache
  * serves every length and G change without being rewritten.
  * Requires Hq % Hkv == 0 and Hq / Hkv <= 8; max_len > 8388608 (2^23)
@@ -338,10 +344,8 @@ int jl_bifocal_decode(const void* q, const void* k_cache, const void* v_cache,
  * device array that the library holds on each device it runs on until the
  * process ends (93 MiB: the table of positions [0, 131072) and 29 MiB of
  * states).  No call allocates or frees device memory.
- *   max_len > 131072, or more than 24 MiB of states counted as
- *   B * Hq * n * 528 bytes with n = min(128, ceil(max_len / 16)) up to B = 64
- *   and n = min(ceil(256 / (B * ceil(Hkv / 4))), 128, ceil(max_len / 16))
- *   beyond -> JL_ERR_UNSUPPORTED, checked on the host before any device work.
+ *   max_len > 131072, or more than 24 MiB of states, counted as the smallest
+ *   workspace is (see jl_decode_workspace_bytes) -> JL_ERR_UNSUPPORTED, checked on the host before any device work.
  * The first call on a device for a given rope_theta builds the table and
  * waits for it on `stream` (make that call outside graph capture); later
  * calls with that theta launch the two decode kernels only.  Every call on a

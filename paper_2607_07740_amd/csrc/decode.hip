@@ -926,9 +926,15 @@ static void decode_geometry(int n_cu, int B, int Hkv, int max_len, int* n_wg, in
   *n_slots = (int)(n + B - 1);
 }
 
-// The count of split slots per head that workspaces are sized by: what the
-// slots need is less for a batch, so a workspace holds them with room to spare
-// up to 64 sequences, and n_wg + B - 1 of them beyond.
+// Bytes of the states and, for a batch, the ends of its sequences
+static size_t slot_bytes(long long n_slots, int B, int Hq) {
+  return (size_t)n_slots * Hq * kStateFloats * sizeof(float) + (B > 1 ? 2 * (size_t)B * sizeof(int) : 0);
+}
+
+// The slots per head that a workspace holds at least: fewer than
+// decode_geometry's for few sequences of few keys, for up to 4 kv heads and
+// beyond 64 sequences.  A call with less than decode_workspace_bytes takes
+// fewer workgroups or several launches (fit_workspace).
 static long long state_slots(int B, int Hkv, int max_len) {
   const long long groups = (long long)B * ((Hkv + kDecHeads - 1) / kDecHeads);
   const long long steps = ((long long)max_len + kDecTile - 1) / kDecTile;
@@ -945,10 +951,33 @@ size_t decode_state_bytes(int B, int Hq, int Hkv, int max_len) {
 size_t decode_workspace_bytes(int B, int Hq, int Hkv, int max_len) {
   int n_wg, n_slots;
   decode_geometry(kDecMaxWg, B, Hkv, max_len, &n_wg, &n_slots);
-  size_t need = (size_t)n_slots * Hq * kStateFloats * sizeof(float);
-  if (B > 1) need += 2 * (size_t)B * sizeof(int);
-  const size_t st = decode_state_bytes(B, Hq, Hkv, max_len);
-  return need > st ? need : st;
+  return std::max(slot_bytes(n_slots, B, Hq), decode_state_bytes(B, Hq, Hkv, max_len));
+}
+
+// What fits a workspace of at least decode_state_bytes: the sequences per
+// launch (a call takes ceil(B / n_seq) of them, one after another in the same
+// workspace), workgroups and slots.  The fewest launches that leave at least
+// half of the workgroups; one sequence a launch fits always (state_slots is B
+// at least, and its one slot is all a single workgroup needs).
+struct DecodeFit {
+  int n_seq, n_wg, n_slots;
+};
+static DecodeFit fit_workspace(int n_cu, int B, int Hq, int Hkv, int max_len, size_t ws_bytes) {
+  DecodeFit f;
+  for (int launches = 1;; ++launches) {
+    f.n_seq = (B + launches - 1) / launches;
+    decode_geometry(n_cu, f.n_seq, Hkv, max_len, &f.n_wg, &f.n_slots);
+    if (slot_bytes(f.n_slots, f.n_seq, Hq) <= ws_bytes) return f;
+    const size_t ends = slot_bytes(0, f.n_seq, Hq);
+    const long long slots =
+        ws_bytes > ends ? (long long)((ws_bytes - ends) / slot_bytes(1, 1, Hq)) : 0;
+    const long long n = slots - (f.n_seq - 1);
+    if (2 * n >= f.n_wg || f.n_seq == 1) {
+      f.n_wg = (int)std::max(1LL, n);
+      f.n_slots = f.n_wg + f.n_seq - 1;
+      return f;
+    }
+  }
 }
 
 size_t decode_map_workspace_bytes(int B, int Hq, int Hkv, int max_len, bool /*freq*/) {
@@ -962,9 +991,27 @@ hipError_t launch_decode(bool bifocal, const uint16_t* q, const uint16_t* kc, co
                          int B, int Hq, int Hkv, int w_pre, int w0, float* ws,
                          hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1,
                          const int32_t* block_table, int max_pages, int n_pages, int page_shift,
-                         const double* freq_og) {
+                         const double* freq_og, size_t ws_bytes) {
   // freq_og: nullptr for the Eq. (3) map, else the frequency map's omega_i
-  // (64) and ramp gamma_i (64); its rows follow the states in ws
+  // (64) and ramp gamma_i (64).  ws holds the states of n_slots splits and,
+  // for a batch, behind them two ints per sequence (split_ends).
+  const DecodeFit fit =
+      fit_workspace(std::min(cu_count(), kDecMaxWg), B, Hq, Hkv, max_len, ws_bytes);
+  if (fit.n_seq < B) {
+    const size_t row = (size_t)Hq * kHeadDim;
+    const size_t cache = block_table != nullptr ? 0 : (size_t)max_len * Hkv * kHeadDim;
+    for (int b = 0; b < B; b += fit.n_seq) {
+      const int n = std::min(fit.n_seq, B - b);
+      const hipError_t e = launch_decode(
+          bifocal, q + b * row, kc + b * cache, vc + b * cache, kv_lens + b, max_len, o + b * row,
+          table, n, Hq, Hkv, w_pre, w0, ws, stream, b == 0 ? ev0 : nullptr,
+          b + n == B ? ev1 : nullptr,
+          block_table != nullptr ? block_table + (size_t)b * max_pages : nullptr, max_pages,
+          n_pages, page_shift, freq_og, ws_bytes);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   DecodeArgs a = {};
   a.q = q;
   a.kc = kc;
@@ -982,7 +1029,8 @@ hipError_t launch_decode(bool bifocal, const uint16_t* q, const uint16_t* kc, co
   a.n_pages = n_pages;
   a.page_shift = page_shift;
   a.n_hgroups = (Hkv + kDecHeads - 1) / kDecHeads;
-  decode_geometry(std::min(cu_count(), kDecMaxWg), B, Hkv, max_len, &a.n_wg, &a.n_slots);
+  a.n_wg = fit.n_wg;
+  a.n_slots = fit.n_slots;
   a.w_pre = w_pre;
   a.w0 = w0;
   a.q_scale = 1.4426950408889634f / sqrtf((float)kHeadDim);

@@ -55,7 +55,7 @@ hipError_t launch_decode(bool bifocal, const uint16_t* q, const uint16_t* kc, co
                          int B, int Hq, int Hkv, int w_pre, int w0, float* ws,
                          hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1,
                          const int32_t* block_table, int max_pages, int n_pages, int page_shift,
-                         const double* freq_og);
+                         const double* freq_og, size_t ws_bytes);
 int noalloc_decode_max_len();
 size_t noalloc_decode_state_bytes();
 size_t noalloc_decode_slot_bytes();
@@ -551,13 +551,14 @@ int decode_common(bool bifocal, const void* q, const void* kc, const void* vc,
     if (e != hipSuccess) return hip_fail(e, "no-alloc decode scratch");
     e = jl::launch_decode(bifocal, (const uint16_t*)q, (const uint16_t*)kc, (const uint16_t*)vc,
                           kv_lens, max_len, (uint16_t*)o, table, B, Hq, Hkv, w_pre, w0, st_ws, s,
-                          nullptr, nullptr, block_table, max_pages, n_pages, page_shift, nullptr);
+                          nullptr, nullptr, block_table, max_pages, n_pages, page_shift, nullptr,
+                          jl::noalloc_decode_slot_bytes());
     if (e != hipSuccess) return hip_fail(e, "decode launch");
     return ok();
   }
-  const size_t need = jl::decode_map_workspace_bytes(B, Hq, Hkv, max_len, freq);
-  if (ws == nullptr || ws_bytes < need)
-    return fail(JL_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, ws_bytes);
+  if (ws == nullptr || ws_bytes < jl::decode_state_bytes(B, Hq, Hkv, max_len))
+    return fail(JL_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu",
+                jl::decode_map_workspace_bytes(B, Hq, Hkv, max_len, freq), ws_bytes);
   if (!aligned16(ws)) return fail(JL_ERR_INVALID_ARG, "workspace must be 16-byte aligned");
   Tables tab{};
   st = get_table(theta, max_len, s, &tab);
@@ -569,7 +570,7 @@ int decode_common(bool bifocal, const void* q, const void* kc, const void* vc,
   hipError_t e = jl::launch_decode(bifocal, (const uint16_t*)q, (const uint16_t*)kc,
                                    (const uint16_t*)vc, kv_lens, max_len, (uint16_t*)o, tab.f32, B,
                                    Hq, Hkv, w_pre, w0, (float*)ws, s, ev0, ev1, block_table,
-                                   max_pages, n_pages, page_shift, freq ? og : nullptr);
+                                   max_pages, n_pages, page_shift, freq ? og : nullptr, ws_bytes);
   if (e != hipSuccess) return hip_fail(e, "decode launch");
   return ok();
 }

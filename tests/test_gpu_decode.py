@@ -206,3 +206,53 @@ def test_decode_equal_ranges(B, Hkv, lens):
                              torch.from_numpy(lens).cuda(), w_pretrained=w_pre, w_local=w0)
     torch.cuda.synchronize()
     assert torch.equal(out.view(torch.int16), paged.view(torch.int16))
+
+
+def _least_slots(B, Hkv, max_len):
+    """Slots per head of the smallest workspace a call accepts, as the header states them."""
+    n = min(128, -(-max_len // 16))
+    if B > 64:
+        n = min(n, -(-256 // (B * -(-Hkv // 4))))
+    return B * n
+
+
+@pytest.mark.parametrize("B,Hkv,max_len", [
+    (1, 2, 4096),   # half of the workgroups
+    (2, 1, 4096),   # one slot short
+    (2, 8, 16),     # a slot a sequence: two launches
+    (33, 4, 32),
+    (64, 4, 16),
+    (80, 8, 704),   # fewer workgroups
+    (300, 8, 48),   # a slot a sequence, beyond 64
+])
+def test_decode_smaller_workspace(B, Hkv, max_len):
+    """Workspaces below jl_decode_workspace_bytes, down to the stated size: the
+    results stay, nothing is written behind the workspace, and less is refused."""
+    g, w_pre, w0 = 2, 128, 50
+    need = _least_slots(B, Hkv, max_len) * g * Hkv * 528
+    assert need < api.decode_workspace_bytes(B, g * Hkv, Hkv, max_len)
+    lens = [1 + (37 * i + max_len // 2) % max_len for i in range(B)]
+    q, kc, vc, lens = synth.decode_inputs(B, g * Hkv, Hkv, max_len, lens, seed=B, nan_tail=True)
+    qd, kd, vd, ld = to_dev(q), to_dev(kc), to_dev(vc), torch.from_numpy(lens).cuda()
+    buf = torch.full((need // 4 + 4096,), float("nan"), dtype=torch.float32, device="cuda")
+    buf[need // 4:] = 7.0
+    want, _, _ = O.decode(q, kc, vc, lens, theta=1e6, w_pretrained=w_pre, w_local=w0)
+    kw = dict(w_pretrained=w_pre, w_local=w0, workspace=buf[:need // 4])
+    for page in (0, 16):
+        say("decode smaller workspace B=%d Hkv=%d max_len=%d page=%d" % (B, Hkv, max_len, page))
+        if page:
+            n = B * max_len // page
+            order = torch.from_numpy(np.random.default_rng(B).permutation(n)).cuda()
+            pools = [torch.empty((n, page, Hkv, 128), dtype=torch.bfloat16, device="cuda")
+                     for _ in range(2)]
+            for pool, c in zip(pools, (kd, vd)):
+                pool[order] = c.view(n, page, Hkv, 128)
+            out = api.decode_paged(qd, *pools, order.to(torch.int32).view(B, -1), ld, **kw)
+        else:
+            out = api.bifocal_decode(qd, kd, vd, ld, **kw)
+        torch.cuda.synchronize()
+        assert_close(to_f64(out), want, what="smaller workspace B=%d" % B)
+        assert bool((buf[need // 4:] == 7.0).all())
+    with pytest.raises(api.JetLongError) as e:
+        api.bifocal_decode(qd, kd, vd, ld, **dict(kw, workspace=buf[:need // 4 - 1]))
+    assert e.value.status == api.JL_ERR_WORKSPACE
