@@ -27,7 +27,9 @@
  *    launched; on any error nothing is written and nothing is launched.
  *  - Where a call allocates or waits.  The library keeps per-device caches
  *    that a call may have to build or grow; only then does it allocate and
- *    wait, and a later call with the same or a smaller shape does neither:
+ *    wait, and a later call with the same shape does neither (nor one with a
+ *    smaller shape, but for the prefill scratch: a call that cuts its blocks
+ *    needs some where a larger call that fills the CUs needs none):
  *      - the RoPE cos/sin table (per device and rope_theta, grown by
  *        doubling to cover the call's positions): every prefill and decode
  *        entry point; growing allocates and waits for `stream`;
@@ -35,7 +37,11 @@
  *        more than 64 sequences, or the frequency map past the window, and of
  *        jl_bifocal_prefill, jl_rope_attention, their _map and _chunk forms
  *        the calls whose query blocks leave CUs idle (see there); growing
- *        waits for `stream`, frees the old buffer and allocates;
+ *        waits for `stream`, frees the old buffer and allocates.  Under
+ *        stream capture it does not grow: a call that would cut its blocks
+ *        runs them whole, a packed call that needs more returns JL_ERR_HIP.
+ *        A buffer that a captured call uses is kept until
+ *        jl_release_caches;
  *      - the frequency-map table (one per device): jl_bifocal_prefill_map
  *        with JL_REMOTE_FREQ; a new (rope_theta, L, w_pretrained) waits for
  *        the whole device, then rebuilds the table in place, or in a buffer

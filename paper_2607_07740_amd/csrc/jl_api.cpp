@@ -128,7 +128,8 @@ struct TableEntry {
 };
 std::mutex g_mu;
 std::vector<TableEntry> g_tables;
-std::vector<std::pair<int, float2*>> g_retired;  // superseded base tables, freed by jl_release_caches
+std::vector<std::pair<int, void*>> g_retired;  // superseded base tables, and scratch that a captured
+                                               // graph uses: freed by jl_release_caches
 
 size_t table_bytes(long long cap) { return (size_t)cap * 64 * (sizeof(float2) + sizeof(uint32_t)); }
 const uint32_t* table16_of(const float2* p, long long cap) {
@@ -286,35 +287,48 @@ int get_freq_table(double theta, int L, int w_pre, hipStream_t stream, Tables* o
 // A packed call's work lists (and frequency-map tables), or the states of a
 // call whose blocks are cut into parts.  One buffer per
 // (device, stream): calls on one stream are ordered, so they can share it; a
-// call that needs more waits for its stream before replacing it.
+// call that needs more waits for its stream before replacing it.  Nothing is
+// allocated under stream capture, and a buffer that a captured call uses is
+// kept when it is replaced, since the graph's replays use it too.
 struct Scratch {
   int device;
   hipStream_t stream;
   size_t bytes;
   void* ptr;
+  bool captured;  // some captured call uses it
 };
 std::vector<Scratch> g_scratch;
 std::mutex g_prefill_mu;  // held from scratch lookup to launch, so a concurrent
                           // call on the same stream cannot replace a buffer in between
 
+// JL_OK with *out = nullptr: the stream is being captured and its buffer is too
+// small.
 int get_scratch(hipStream_t stream, size_t bytes, void** out) {
+  *out = nullptr;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cs) != hipSuccess) (void)hipGetLastError();
+  const bool capturing = cs != hipStreamCaptureStatusNone;
   std::lock_guard<std::mutex> lock(g_mu);
   Scratch* found = nullptr;
   for (auto& sc : g_scratch)
     if (sc.device == dev && sc.stream == stream) found = &sc;
   if (found && found->bytes >= bytes) {
+    found->captured |= capturing;
     *out = found->ptr;
     return JL_OK;
   }
+  if (capturing) return JL_OK;
   if (found) {
     e = hipStreamSynchronize(stream);  // earlier calls on this stream may still read it
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-    (void)hipFree(found->ptr);
-    found->ptr = nullptr;
-    found->bytes = 0;
+    if (found->captured)
+      g_retired.emplace_back(dev, found->ptr);
+    else
+      (void)hipFree(found->ptr);
+    *found = Scratch{dev, stream, 0, nullptr, false};
   }
   const size_t want = bytes + bytes / 8;  // some room for growth
   void* p = nullptr;
@@ -324,7 +338,7 @@ int get_scratch(hipStream_t stream, size_t bytes, void** out) {
     found->ptr = p;
     found->bytes = want;
   } else {
-    g_scratch.push_back(Scratch{dev, stream, want, p});
+    g_scratch.push_back(Scratch{dev, stream, want, p, false});
   }
   *out = p;
   return JL_OK;
@@ -411,7 +425,7 @@ int prefill_common(bool bifocal, const void* q, const void* k, const void* v, vo
   }
   // where the blocks of the call leave CUs idle they are cut into parts, whose
   // states go to the stream's scratch
-  const int n_cu = literal ? 1 : jl::cu_count();  // 1: no block is cut (no library scratch)
+  int n_cu = literal ? 1 : jl::cu_count();  // 1: no block is cut (no library scratch)
   void* states = nullptr;
   std::unique_lock<std::mutex> launch_lock(g_prefill_mu, std::defer_lock);
   const size_t state_bytes = jl::prefill_chunk_workspace_bytes(n_cu, use_bifocal, B, Hq, Hkv,
@@ -420,6 +434,7 @@ int prefill_common(bool bifocal, const void* q, const void* k, const void* v, vo
     launch_lock.lock();
     st = get_scratch(s, state_bytes, &states);
     if (st != JL_OK) return st;
+    if (states == nullptr) n_cu = 1;  // captured before the scratch was made: whole blocks
   }
   hipEvent_t ev0, ev1;
   timing_events(0, &ev0, &ev1);
@@ -478,6 +493,9 @@ int prefill_varlen(bool bifocal, const void* q, const void* k, const void* v, vo
     launch_lock.lock();
     st = get_scratch(s, scratch_bytes, &scratch);
     if (st != JL_OK) return st;
+    if (scratch == nullptr)
+      return fail(JL_ERR_HIP, "packed prefill: %zu bytes of scratch cannot be allocated under "
+                  "stream capture (make the call once before)", scratch_bytes);
   }
   double og[128];
   if (freq) freq_map_ramp(theta, w_pre, og);

@@ -54,3 +54,56 @@ def test_split_blocks(P, n, B, Hkv, g, w_pre, w0, rescale):
     assert np.isfinite(to_f64(out)).all()
     assert_close(lse.cpu().numpy()[rows[:, 0], rows[:, 1], rows[:, 2] - P], want_lse, max_abs=5e-2,
                  mean_abs=5e-3, what="split lse")
+
+
+def test_cut_call_under_capture_needs_no_allocation():
+    """A stream whose calls so far needed no scratch captures a call that would
+    be cut: the call runs whole blocks instead of allocating inside the capture.
+    After an eager call of that shape the capture cuts as the eager call does,
+    and its replays stay good when a larger call replaces the scratch."""
+    Hq, Hkv, P, n = 8, 2, 9000, 64
+    q, k, v = (to_dev(x) for x in synth.prefill_inputs(1, Hq, Hkv, P + n, 128, seed=3))
+    kw = dict(w_pretrained=2048, w_local=500)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        big = torch.randn((8, 4096, 32, 128), device="cuda").to(torch.bfloat16)  # fills the CUs
+        kv = big[:, :, :8].contiguous()
+        api.bifocal_prefill(big, kv, kv, **kw)
+        api.rope_attention_decode(q[:, -1].contiguous(), k, v,  # the RoPE table covers the call
+                                  torch.tensor([P + n], dtype=torch.int32, device="cuda"))
+        qc, out = q[:, P:].contiguous(), torch.empty_like(q[:, P:].contiguous())
+        torch.cuda.synchronize()
+
+        def captured():
+            say("cut chunk, captured")
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                api.prefill_chunk(qc, k, v, q_start=P, out=out, **kw)
+            outs = []
+            for _ in range(3):
+                out.fill_(float("nan"))
+                graph.replay()
+                torch.cuda.synchronize()
+                outs.append(out.clone())
+            assert all(torch.equal(o.view(torch.int16), outs[0].view(torch.int16)) for o in outs)
+            return graph, outs[0]
+
+        _, whole = captured()
+        say("cut chunk, eager")
+        eager = api.prefill_chunk(qc, k, v, q_start=P, **kw)
+        torch.cuda.synchronize()
+        graph, cut = captured()
+        say("larger cut chunk, then the graph again")  # its states must not lie in freed memory
+        api.prefill_chunk(big[:1, :1000], k, v, q_start=P - 1000, w_pretrained=2048, w_local=500)
+        filler = [torch.full((1 << 20,), float("nan"), device="cuda") for _ in range(40)]
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        del filler
+        assert torch.equal(out.view(torch.int16), cut.view(torch.int16))
+    assert torch.equal(cut.view(torch.int16), eager.view(torch.int16))
+    full = api.bifocal_prefill(q, k, v, **kw)[:, P:]
+    torch.cuda.synchronize()
+    assert_close(to_f64(whole), to_f64(full), what="captured whole blocks")
+    assert_close(to_f64(cut), to_f64(full), what="captured parts")
