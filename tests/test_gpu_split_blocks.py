@@ -56,6 +56,76 @@ def test_split_blocks(P, n, B, Hkv, g, w_pre, w0, rescale):
                  mean_abs=5e-3, what="split lse")
 
 
+@pytest.mark.parametrize("rescale", [None, 3.0])
+@pytest.mark.parametrize("P,n,B,Hkv,g,w_pre,w0", [
+    (3000, 64, 1, 8, 4, 1024, 300),    # 8 blocks, all cut, one per XCD
+    (2900, 130, 3, 8, 4, 1 << 20, 0),  # 72 blocks of three q blocks a group, G = 1
+    (9000, 2100, 1, 8, 4, 2048, 500),  # 256 whole blocks and the last wave's 8 in parts
+    (6000, 1370, 2, 3, 8, 2048, 500),  # 256 and 2, groups no multiple of the XCDs
+])
+def test_cut_blocks_in_the_grid(P, n, B, Hkv, g, w_pre, w0, rescale):
+    """Whole blocks in front of a cut last wave, and cut blocks in the XCD order
+    (kv heads times sequences a multiple of 8): rows of every query block, its
+    first and last, against the oracle, over a poisoned output."""
+    T, Hq, page, bq = P + n, g * Hkv, 64, 256 // g
+    q, k, v = synth.prefill_inputs(B, Hq, Hkv, T, 128, seed=T + g, outlier_channels=8)
+    pages = -(-T // page)
+    pad = [(0, 0), (0, pages * page - T), (0, 0), (0, 0)]
+    kd, vd = (to_dev(np.pad(x, pad, constant_values=0x7FC0)) for x in (k, v))
+    qd = to_dev(q[:, P:])
+    table = torch.arange(B * pages, dtype=torch.int32, device="cuda").view(B, pages)
+    kw = dict(q_start=P, w_pretrained=w_pre, w_local=w0, want_lse=True)
+    old = api.debug_prefill_rescale_log2(rescale) if rescale else None
+    try:
+        say("cut blocks in the grid P=%d n=%d B=%d rescale=%s" % (P, n, B, rescale))
+        out, lse = api.prefill_chunk(qd, kd, vd, out=torch.full_like(qd, float("nan")), **kw)
+        say("cut blocks in the grid, paged")
+        pg, pl = api.prefill_chunk_paged(qd, kd.view(-1, page, Hkv, 128),
+                                         vd.view(-1, page, Hkv, 128), table,
+                                         out=torch.full_like(qd, float("nan")), **kw)
+        torch.cuda.synchronize()
+    finally:
+        if rescale:
+            api.debug_prefill_rescale_log2(old)
+    assert torch.equal(out.view(torch.int16), pg.view(torch.int16))
+    assert torch.equal(lse.view(torch.int32), pl.view(torch.int32))
+    assert bool(torch.isfinite(out.float()).all()) and bool(torch.isfinite(lse).all())
+    starts = range(P, T, bq)
+    pos = sorted({x for s in starts for x in (s, min(s + bq, T) - 1)})
+    rows = np.array([[b, h, x] for b in range(B) for i, x in enumerate(pos)
+                     for h in {i % Hq, (i + bq) % Hq, Hq - 1 - i % Hq}], dtype=np.int64)
+    want, want_lse, _ = O.prefill_rows(q, k, v, rows, theta=1e6, w_pretrained=w_pre, w_local=w0,
+                                       want_lse=True)
+    assert_close(to_f64(out)[rows[:, 0], rows[:, 2] - P, rows[:, 1]], want, what="cut in the grid")
+    assert_close(lse.cpu().numpy()[rows[:, 0], rows[:, 1], rows[:, 2] - P], want_lse, max_abs=5e-2,
+                 mean_abs=5e-3, what="cut lse")
+
+
+def test_cut_calls_on_two_streams():
+    """Cut calls that overlap on two streams, each with its own states, one of
+    them growing its scratch while the other runs: the bits of calls made alone."""
+    Hq, Hkv, P = 8, 2, 6000
+    shapes = [64, 200, 520]  # more parts each: the scratch grows
+    q, k, v = (to_dev(x) for x in synth.prefill_inputs(1, Hq, Hkv, P + 520, 128, seed=8))
+    chunks = [(q[:, P:P + n].contiguous(), k[:, :P + n].contiguous(), v[:, :P + n].contiguous())
+              for n in shapes]
+    kw = dict(q_start=P, w_pretrained=2048, w_local=500)
+    alone = [api.prefill_chunk(*c, **kw) for c in chunks]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    say("cut chunks on two streams")
+    got = []
+    for i in range(6):
+        for j, st in enumerate(streams):
+            m = (i // 2 if j == 0 else 2 - i // 2)  # one grows, the other starts large
+            out = torch.empty_like(chunks[m][0])
+            api.prefill_chunk(*chunks[m], out=out, stream=st, **kw)
+            got.append((m, out))
+    torch.cuda.synchronize()
+    for m, out in got:
+        assert torch.equal(out.view(torch.int16), alone[m].view(torch.int16)), m
+
+
 def test_cut_call_under_capture_needs_no_allocation():
     """A stream whose calls so far needed no scratch captures a call that would
     be cut: the call runs whole blocks instead of allocating inside the capture.
