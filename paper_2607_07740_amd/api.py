@@ -152,9 +152,13 @@ def _stream(stream):
     if stream is not None:
         return stream.cuda_stream
     # the raw handle: building a Stream object for it takes 3 us, a fifth of a
-    # small decode call's time on the host
-    c = _t()._C
-    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    # small decode call's time on the host.  Its entry is not part of torch's
+    # public interface, so a torch without it gets the object.
+    torch = _t()
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _dev(t, name, dtype=None, shape=None, device=None):

@@ -320,3 +320,28 @@ def test_literal_workspace_size_and_rejections():
     assert _literal(ws=P(0x1010)) == api.JL_ERR_INVALID_ARG  # not 256-byte aligned
     assert _literal(o=None) == api.JL_ERR_INVALID_ARG
     assert _literal(w=0) == api.JL_ERR_INVALID_ARG
+
+
+def test_stream_handle_without_torchs_private_entry(monkeypatch):
+    """The current stream's handle comes from the public interface where torch has
+    no raw one, and from a stream that the caller gives otherwise."""
+    class Stream:
+        cuda_stream = 0x1234
+
+    class Bare:
+        _C = object()
+
+        class cuda:
+            current_stream = staticmethod(lambda: Stream)
+
+    monkeypatch.setattr(api, "_torch", Bare)
+    assert api._stream(None) == 0x1234
+    assert api._stream(Stream) == 0x1234
+
+    class Raw(Bare):
+        class _C:
+            _cuda_getDevice = staticmethod(lambda: 3)
+            _cuda_getCurrentRawStream = staticmethod(lambda dev: 0x100 + dev)
+
+    monkeypatch.setattr(api, "_torch", Raw)
+    assert api._stream(None) == 0x103
