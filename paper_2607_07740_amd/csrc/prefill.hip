@@ -1043,18 +1043,31 @@ static hipError_t launch_split_blocks(const PrefillArgs& a, hipStream_t stream) 
 }
 
 // How a fused or vanilla call of Lq queries behind q_start is cut; times are in
-// tile visits, of about 1.5 us.  A workgroup fills a CU, so blocks run in waves
-// of n_cu.  Blocks of about equal length (a chunk far into a sequence) are
-// only cut where they make up the last, partial wave; blocks of very
-// different lengths (a prefill from position 0) fill the CUs among themselves
-// unless there are fewer blocks than CUs.  A part costs kPartCost visits to
-// start, the merge kMergeCost to launch and kStateCost per part to write and
-// read its state; the cheapest number of parts is taken if it saves a tenth.
-// Measured, whole blocks against parts: 512 queries behind 36011 keys, 32/8
-// heads, 896 -> 357 us (64 blocks in 4 parts: 322 us and a 9 us merge); 128
-// behind 30000 713 -> 102; 1024 behind 49976, 16/8 heads, 1242 -> 490; 3000
-// behind 17000 (375 blocks: 256 whole, 119 in 2 parts) 967 -> 867; a prefill of
-// 8192, 4/1 heads, 195 -> 125.
+// tile visits, of 1.4 (part of the CUs busy) to 1.95 us (all of them).  A
+// workgroup fills a CU, so blocks run in waves of n_cu.
+//   - Calls of at least n_cu blocks are cut only in their last, partial wave, and
+//     only where the shortest block has 0.8 of the longest's visits or more and
+//     the calls are few waves: otherwise blocks of different lengths fill the CUs.
+//   - The parts of fewer blocks run in waves of their own where the shortest has
+//     0.65 of the longest's visits; below, they fill the CUs among themselves
+//     (1.2 times the mean work of a CU).
+//   - A block of 31 visits stays whole.  Where a call has such blocks beside ones
+//     of up to kHalfVisits, and may run half blocks, those are sooner.
+// A part costs kPartCost visits to start, the merge kMergeCost to launch and
+// kStateCost per part to write and read its state; the cheapest number of parts
+// is taken if it saves a tenth by that count (by the clock, of 79 calls measured
+// both ways the choice is slower in four, by 1 to 4%: 700 queries behind 1800,
+// 32/8 heads, 62.7 -> 65.5).
+// Measured, whole (or half) blocks -> parts, us.  Few blocks, nearly even: 512
+// queries behind 36011 keys, 32/8 heads, paged, 898 -> 313; 128 behind 30000 713 -> 102;
+// 1024 behind 49976, 16/8 heads, 1242 -> 490; 1500 behind 3500 119 -> 81.  More
+// parts than CUs: 2600 behind 7000, 16/8 heads (168 blocks), 215 -> 204, and 234
+// counted as uneven.  Last wave: 3000 behind 17000, 32/8 heads (256 + 120
+// blocks), 898 -> 831; 4000 behind 17000 (256 + 248, not cut) 1069, 1137 in parts.
+// Uneven: prefills of 3000, 6000 and 16000 tokens, 4/1 heads, 71 -> 62,
+// 135 -> 72, 355 -> 289; 8192, 8/2 heads (256 blocks, not cut) 191.
+// Beside blocks of 31 visits: 2000 tokens, 4/1 heads, half blocks 50, parts 60;
+// 2400 59 and 61; 2560, 8/8 heads, 64 and 60.
 struct PrefillSplit {
   int n_whole, n_tail, n_part;  // n_part = 1: no block is cut
 };
@@ -1062,14 +1075,15 @@ struct PrefillSplit {
 static PrefillSplit prefill_split(int n_cu, long long n_blocks, int q_start, int Lq, int BQ,
                                   int w0) {
   constexpr double kPartCost = 4, kMergeCost = 5, kStateCost = 0.044;
-  constexpr int kMaxParts = 16;
+  constexpr int kMaxParts = 16, kHalfVisits = 40;
   PrefillSplit none = {(int)n_blocks, 0, 1};
   const int n_qb = (Lq + BQ - 1) / BQ;
   const int q_last = q_start + (n_qb - 1) * BQ;
   const int n_max = block_visits(q_last, q_start + Lq - 1, w0);
   const int n_min = block_visits(q_start, std::min(q_start + BQ, q_start + Lq) - 1, w0);
-  const bool even = n_min >= 0.8 * n_max;
-  if (n_blocks >= n_cu && (!even || n_blocks > 4LL * n_cu)) return none;
+  const bool even = n_min >= 0.65 * n_max;
+  if (2 * n_blocks <= n_cu && BQ >= 2 && n_min < 2 * kMinPart && n_max < kHalfVisits) return none;
+  if (n_blocks >= n_cu && (n_min < 0.8 * n_max || n_blocks > 4LL * n_cu)) return none;
   const int tail = (int)(n_blocks % n_cu);
   if (tail == 0) return none;
   PrefillSplit best = none;

@@ -224,6 +224,7 @@ def test_varlen_entries_without_planning_kernel(g, w, lens):
 @pytest.mark.parametrize("Hq,Hkv,L", [
     (2, 1, 1), (16, 8, 1000), (16, 8, 2048), (16, 8, 2049), (8, 8, 129),
     (128, 1, 70), (256, 1, 40),  # blocks of 2 positions, halved; of 1, which cannot be
+    (4, 1, 2300),  # blocks of up to 36 visits, beside ones too short for two parts: not cut
 ])
 def test_half_blocks_equal_whole_blocks(Hq, Hkv, L):
     """A call of at most half as many blocks as CUs runs blocks of half the rows
