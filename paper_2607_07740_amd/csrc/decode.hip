@@ -762,6 +762,9 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_split_kernel(DecodeArgs
   }
   __syncthreads();  // the merged states are read: the next split may fill the buffers
   }
+  // a workgroup without a split leaves its offset rows' copies to land while it
+  // still holds the LDS they go to
+  wait_vmem();
 }
 
 // Final merge over the splits of one head (Eq. (7) weights exp2(m - M)):
