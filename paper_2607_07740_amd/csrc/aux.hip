@@ -53,7 +53,7 @@ hipError_t launch_build_table(float2* table, uint32_t* table16, int n_pos, const
 // sequence's rows equal the table of a call on that sequence alone.  One
 // workgroup per key-tile entry of the packed batch's plan.
 struct PackedFreqArgs {
-  const int4* twork;  // per key tile: (seq0, L, tile, tile0); L <= 0 marks an unused entry
+  const int4* twork;  // per key tile: (seq0, L, tile, 0); L <= 0 marks an unused entry
   float2* table;
   uint32_t* table16;
   int w_pre;

@@ -102,9 +102,9 @@ struct PrefillArgs {
   float slack;    // log2 units a tile maximum may lie above (or, before anything
                   // was accumulated, below) the reference before it moves (64)
   float* o32;     // window passes: normalised fp32 O_X [B][L][Hq][128]
-  // packed variable-length batch (nullptr otherwise): one (seq0, L, q block,
-  // first tile) per Hkv consecutive workgroups; q and o are [T][Hq][128] with
-  // T = Lq, lse is [Hq][T] and each sequence takes its own
+  // packed variable-length batch (nullptr otherwise): one (seq0, L, q block, 0)
+  // per Hkv consecutive workgroups (16 bytes, one load); q and o are
+  // [T][Hq][128] with T = Lq, lse is [Hq][T] and each sequence takes its own
   // G = group_size(L, w_pre)
   const int4* qwork;
   int w_pre;
@@ -1230,9 +1230,8 @@ hipError_t launch_prefill_literal(const uint16_t* q, const uint16_t* k, const ui
 // Sequence s of a packed batch holds rows cu[s] .. cu[s + 1] - 1 of q, k, v
 // and o.  Its bounds are clamped into [0, T] (a non-increasing entry gives an
 // empty sequence) and its length to max_len.  The work lists hold one
-// (seq0, L, index, first tile) per query block (index = block, last block
-// first) and, for the frequency map's tables, per key tile (index = tile);
-// their sizes nq = ceil(T / BQ) + B and
+// (seq0, L, index, 0) per query block (index = block, last block first) and, for
+// the frequency map's tables, per key tile (index = tile); their sizes nq = ceil(T / BQ) + B and
 // nt = ceil(T / 64) + B bound the totals of any well-formed cu.  A sequence
 // whose entries would run past either list (possible only for malformed
 // cu) gets none: its output rows are left untouched.  Every list entry is
@@ -1291,16 +1290,14 @@ __global__ __launch_bounds__(kPlanThreads) void varlen_plan_kernel(PlanArgs a) {
       const int j = owner(inc_q, e);
       const int nb = (s_len[j] + a.BQ - 1) / a.BQ;
       const long long i = e - (inc_q[j] - nb);
-      const long long toff = base_t + inc_t[j] - (s_len[j] + kPfBK - 1) / kPfBK;
-      a.qwork[base_q + e] = fits(j) ? int4{s_seq0[j], s_len[j], (int)(nb - 1 - i), (int)toff}
+      a.qwork[base_q + e] = fits(j) ? int4{s_seq0[j], s_len[j], (int)(nb - 1 - i), 0}
                                     : int4{0, 0, 0, 0};
     }
     for (long long e = t; a.twork != nullptr && e < tot_t && base_t + e < a.nt; e += kPlanThreads) {
       const int j = owner(inc_t, e);
       const int nk = (s_len[j] + kPfBK - 1) / kPfBK;
       const long long i = e - (inc_t[j] - nk);
-      a.twork[base_t + e] = fits(j) ? int4{s_seq0[j], s_len[j], (int)i, (int)(inc_t[j] - nk + base_t)}
-                                    : int4{0, 0, 0, 0};
+      a.twork[base_t + e] = fits(j) ? int4{s_seq0[j], s_len[j], (int)i, 0} : int4{0, 0, 0, 0};
     }
     base_q += tot_q;
     base_t += tot_t;
