@@ -109,7 +109,9 @@ int64_t jl_group_size(int64_t L, int64_t w_pretrained);
  * positions of one sequence and kv head), or whose blocks make up a few whole
  * waves of the CUs and a small rest, cuts the idle CUs' share of its blocks
  * into parts of the key range and merges their fp32 states (133 KB per part, at
- * most 16 parts a block, in the prefill scratch); others need no scratch.
+ * most 16 parts a block, in the prefill scratch); others need no scratch.  So the
+ * bits of such a call depend on the count of CUs and on the size of the batch, by
+ * the order of the fp32 sums over the parts.
  * q, k, v are only read.
  */
 int jl_bifocal_prefill(const void* q, const void* k, const void* v, void* o, float* lse, int B,
@@ -267,8 +269,8 @@ int jl_rope_attention(const void* q, const void* k, const void* v, void* o, floa
  * Bytes of device workspace jl_bifocal_prefill_literal needs for this shape:
  * 3 * B * L * Hq * head_dim * 4 (the window outputs) + the window LSEs
  * (3 * B * Hq * L * 4, rounded up to 256) + B * Hkv * ceil(L / 64) * 16 KB +
- * 256 + 4 * B * Hkv * L (a region that is not used).  Returns 0 for invalid
- * arguments.
+ * 256 + 4 * B * Hkv * L (a region that is not used and stays part of the size).
+ * Returns 0 for invalid arguments.
  */
 size_t jl_prefill_literal_workspace_bytes(int B, int Hq, int Hkv, int L, int head_dim);
 
@@ -277,8 +279,8 @@ size_t jl_prefill_literal_workspace_bytes(int B, int Hq, int Hkv, int L, int hea
  * attention calls A (band q - k <= w_local, base rotation), B (all causal
  * keys, remote rotation) and C (band, remote rotation) run as three calls
  * of the attention kernel (each as the fused call runs: a fast pass, then the
- * checked pass of the blocks that need it), each writing its normalised output O_X and its natural-log LSE_X, and a fourth
- * kernel merges them per row with
+ * checked pass of the blocks that need it), each writing its normalised output
+ * O_X and its natural-log LSE_X, and a fourth kernel merges them per row with
  *   M = max(LSE_A, LSE_B, LSE_C), W_X = exp(LSE_X - M),
  *   O = (W_A O_A + (W_B O_B - W_C O_C)) / (W_A + (W_B - W_C)),
  *   lse = M + ln(W_A + (W_B - W_C)),
@@ -294,8 +296,10 @@ size_t jl_prefill_literal_workspace_bytes(int B, int Hq, int Hkv, int L, int hea
  *     (x = 0, 1, 2), O_X as fp32 [B, L, Hq, head_dim] at float offset
  *     x * B * L * Hq * head_dim, and LSE_X as fp32 [B, Hq, L] at float offset
  *     3 * B * L * Hq * head_dim + x * B * Hq * L.
- * When G == 1 the call runs the vanilla kernel, as jl_bifocal_prefill does;
- * the window outputs and LSEs are left unwritten.  Either way no library
+ * When G == 1 the call runs the vanilla kernel, as jl_bifocal_prefill does, but
+ * never cuts its blocks: the same bits where that call cuts none, and equal up to
+ * the order of the fp32 sums over the parts otherwise.  The window outputs and
+ * LSEs are left unwritten.  Either way no library
  * scratch is used (only the RoPE table cache, as for every entry point).
  */
 int jl_bifocal_prefill_literal(const void* q, const void* k, const void* v, void* o, float* lse,

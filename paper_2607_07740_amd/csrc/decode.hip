@@ -275,11 +275,11 @@ __device__ inline float max_xor16_32(float x) {
 // is copied to LDS the same way, in front of the first steps, so nothing in
 // the prologue is waited for on its own.
 //
-// Bound by HBM: 1.23 us per 32 KB step and CU at 6.8 TB/s.  A call of 131072
-// keys, 32/8 heads, takes 84.9 us (6.3 TB/s in all; 88.9 before the prologue,
-// the value reads and the maxima below left the critical path); 8 sequences
-// of 32K to 128K 391 us (6.9 TB/s; 397); 32 paged ones of 0.5K to 16K 116 us
-// (148).  Requesting every LDS operand of a step at once took 3.5 us more:
+// Bound by HBM: 1.22 us per 32 KB step and CU at the 6.9 TB/s that the copies
+// alone reach.  A call of 131072 keys, 32/8 heads, takes 85 us (6.3 TB/s in all;
+// 89 before the prologue, the value reads and the maxima below left the critical
+// path); 8 sequences of 32K to 128K 395 us (6.8 TB/s; 402); 32 paged ones of 0.5K
+// to 16K 118 us (148).  Requesting every LDS operand of a step at once took 3.5 us more:
 // the bursts hold up the copies' writes.
 //
 // Rotation by tile offset: with k0 the step's first key, a key at k0 + t is

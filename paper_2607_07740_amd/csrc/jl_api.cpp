@@ -477,8 +477,8 @@ int prefill_varlen(bool bifocal, const void* q, const void* k, const void* v, vo
     return fail(JL_ERR_INVALID_ARG, "problem too large");
   const int max_len = std::min(max_seqlen, T);  // no sequence is longer than T
   // No sequence past the window: G = 1 for all, and the vanilla kernel gives the
-  // fused one's bits in less time (8192 tokens, 32/8 heads, 522 -> 500 us; 32768
-  // 7875 -> 7550).  Longer batches mix G, so one launch must be fused.
+  // fused one's bits in less time (8192 tokens, 32/8 heads, 522 -> 508 us; 32768
+  // 7873 -> 7530).  Longer batches mix G, so one launch must be fused.
   if (bifocal && max_len <= w_pre) bifocal = false;
   const bool freq = bifocal && remote_map == JL_REMOTE_FREQ;
   Tables tab{};

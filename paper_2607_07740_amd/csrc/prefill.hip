@@ -37,12 +37,12 @@
 // The common path is exp2, convert and a dot product for the row sum.  A
 // first, fast pass never moves the reference: it only notes, per tile, whether
 // a row's probability sum passed 2^64 and, at the end, whether a row's total
-// fell below 2^-64; a block that trips either writes nothing and is run again
-// by the same workgroup with the checked pass, which tests each tile's probability sum after its softmax and, in a rare branch,
-// moves the reference to the tile's largest score (when that lies more than 64
-// above it, or more than 64 below it before anything was accumulated),
-// re-bases the tile and rescales the state.  So every probability stays below
-// 2^64.
+// fell below 2^-64; a block that trips either writes no output and is run
+// again by the same workgroup with the checked pass, which tests each tile's
+// probability sum after its softmax and, in a rare branch, moves the reference
+// to the tile's largest score (when that lies more than 64 above it, or more
+// than 64 below it before anything was accumulated), re-bases the tile and
+// rescales the state.  So every probability stays below 2^64.
 #include <algorithm>
 #include <climits>
 
@@ -292,7 +292,7 @@ __device__ inline float* part_state(const PrefillArgs& a, int tail_block, int pa
 // to `state` (parts > 1).  SAFE = false: the fast pass.  It never waits on the
 // softmax reference check; instead it records, without a branch, whether any
 // tile's probability sum exceeded 2^slack, and at the end whether a row's
-// total fell below 2^-slack.  A block with either writes nothing and returns
+// total fell below 2^-slack.  A block with either writes no output and returns
 // true; the kernel then runs it again with SAFE = true: the per-tile check,
 // which moves the reference as needed.  Every mode runs so.
 template <int MODE, bool SAFE, bool PAGED, bool SPLIT, int WAVES>
@@ -973,7 +973,8 @@ __global__ __launch_bounds__(256) void literal_merge_kernel(MergeArgs a) {
 // Literal mode workspace: O_A, O_B, O_C (fp32 [B][L][Hq][128] each), then
 // LSE_A, LSE_B, LSE_C (fp32 [B][Hq][L] each), then at the next 256-byte
 // boundary a region of 16 KB per key tile and kv head and 4 bytes per key and
-// kv head that the size has always included; nothing uses it.
+// kv head.  Nothing uses that region: it is part of the size that the header
+// states, by which callers that do not ask allocate.
 static size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 size_t literal_workspace_bytes(int B, int Hq, int Hkv, int L) {
   const size_t rows = (size_t)B * L * Hq;

@@ -310,8 +310,9 @@ def test_literal_workspace_size_and_rejections():
     n = api.prefill_literal_workspace_bytes(B, Hq, Hkv, L)
     o_bytes = 3 * B * L * Hq * 128 * 4
     lse_bytes = -(-3 * B * Hq * L * 4 // 256) * 256
-    img = B * Hkv * (-(-L // 64)) * 16384  # V^T tile images only: K is read raw
-    retry = 256 + 4 * B * Hkv * L  # the windows' counters and list of blocks for the checked rerun
+    # a region that no kernel uses: it stays part of the size that the header states
+    img = B * Hkv * (-(-L // 64)) * 16384
+    retry = 256 + 4 * B * Hkv * L
     assert n == o_bytes + lse_bytes + img + retry
     assert api.prefill_literal_workspace_bytes(B, 7, Hkv, L) == 0
     assert api.prefill_literal_workspace_bytes(B, Hq, Hkv, L, 64) == 0

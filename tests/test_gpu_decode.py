@@ -94,10 +94,9 @@ def test_decode_deterministic_and_workspace_contents_irrelevant():
 
 @pytest.mark.parametrize("B", [2, 64, 65])
 def test_decode_batch_split_plans(B):
-    """Split counts balanced over the actual lengths (B <= 64: one short and
-    long sequences side by side, so most workgroups go to the long ones) and
-    the max_len-based split of larger batches (B = 65); NaN tails catch any
-    read past a length."""
+    """Equal ranges of the batch's steps over short and long sequences side by
+    side, planned by one lane per sequence (B <= 64) and by a workgroup-wide scan
+    (B = 65); NaN tails catch any read past a length."""
     Hq, Hkv, w_pre, w0, max_len = 8, 8, 512, 100, 4096
     rng = np.random.default_rng(B)
     lens = [int(x) for x in rng.integers(1, max_len + 1, size=B)]

@@ -104,11 +104,11 @@ def test_literal_agrees_with_fused():
 
 
 def test_literal_windows_checked_rerun():
-    """Each window pass runs a fast pass and reruns the blocks it lists with
-    the checked kernel.  With the rescale bound lowered to 2^3 nearly every
-    block of every window is listed; the merged output and the three window
-    states must still match the oracle, and equal what the same call gives at
-    the default bound to the tolerance."""
+    """Each window pass runs a block's fast pass and, where that trips the check,
+    its checked pass.  With the rescale bound lowered to 2^3 nearly every block of
+    every window is run again; the merged output and the three window states must
+    still match the oracle, and equal what the same call gives at the default
+    bound to the tolerance."""
     B, Hq, Hkv, L, w_pre, w0 = 1, 8, 2, 517, 100, 40
     q, k, v = synth.prefill_inputs(B, Hq, Hkv, L, 128, seed=91, outlier_channels=8)
     old = api.debug_prefill_rescale_log2(3.0)
@@ -147,9 +147,10 @@ def test_literal_within_window_is_vanilla():
 
 def test_literal_within_window_allocates_nothing():
     """G == 1 at the 32K within-window shape: the vanilla kernel the literal
-    entry runs stages its value tiles in the caller's workspace, so the call
-    adds no device memory once the RoPE table covers L (a decode of the same
-    length builds that table first), and it still equals the vanilla call."""
+    entry runs needs no scratch (its blocks are never cut), so the call adds no
+    device memory once the RoPE table covers L (a decode of the same length
+    builds that table first), and it still equals the vanilla call, which fills
+    the CUs and is not cut either."""
     B, Hq, Hkv, L = 1, 32, 8, 32768
     q, k, v = (to_dev(x) for x in synth.prefill_inputs(B, Hq, Hkv, L, 128, seed=8))
     out = torch.empty_like(q)

@@ -106,8 +106,8 @@ def test_rescale_path_on_every_tile(bifocal, L, g, w_pre, w0):
 def test_rescale_rerun_list_holds_every_block(g, Hkv):
     """Wide GQA groups give query blocks of a few positions (one at g = 256),
     so a 300-token call has up to 300 blocks per kv head.  With the bound
-    lowered to 2^3 nearly every block is flagged and listed for the checked
-    rerun; the list must hold them all and the result must still match the
+    lowered to 2^3 nearly every block trips the check and is run again by its
+    own workgroup with the checked pass; the result must still match the
     oracle."""
     B, L, w_pre, w0 = 1, 300, 70, 20
     q, k, v = synth.prefill_inputs(B, g * Hkv, Hkv, L, 128, seed=g, outlier_channels=8)
