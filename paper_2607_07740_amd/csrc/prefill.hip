@@ -96,6 +96,7 @@ struct PrefillArgs {
   int B, Hq, Hkv, L;     // L: keys [0, L), the call's sequence length (G follows it)
   int q_start, Lq;              // query rows: positions q_start .. q_start + Lq - 1 (= L - Lq ..)
   int g, BQ, n_qblocks;
+  int in_turn;    // vanilla kernel: all XCDs take the (sequence, kv head) groups one after another
   int w0;         // local window; INT_MAX for the vanilla kernel and window B
   FastDiv gdiv;   // division by G (Eq. (3))
   float q_scale;  // log2(e) / sqrt(head_dim): scores come out in log2 units
@@ -177,6 +178,7 @@ __device__ inline int4 plan_entry(const PrefillArgs& a, int item) {
 }
 
 // false: no query block here (an unused entry of a packed batch's plan)
+template <bool VANILLA>
 __device__ inline bool work_of(const PrefillArgs& a, int bid, bool fused, Work& W) {
   const int n_groups = a.B * a.Hkv;
   if (a.qwork != nullptr || a.cu != nullptr) {
@@ -201,7 +203,7 @@ __device__ inline bool work_of(const PrefillArgs& a, int bid, bool fused, Work& 
   } else {
     int group;
     if ((n_groups & 7) == 0) {
-      const int work = (bid & 7) * (a.n_blocks >> 3) + (bid >> 3);
+      const int work = VANILLA && a.in_turn ? bid : (bid & 7) * (a.n_blocks >> 3) + (bid >> 3);
       group = work / a.n_qblocks;
       W.qblk = a.n_qblocks - 1 - (work - group * a.n_qblocks);
     } else {
@@ -445,10 +447,18 @@ __device__ __forceinline__ bool prefill_block(const PrefillArgs& a, const Work& 
     const uint32_t* tr =
         (e.remote ? rtable16 : a.table16) + (size_t)(e.row0 + row) * kHalf + 8 * rt_c;
     RotIn r;
+    // the vanilla kernel reads a row of its own for every key, 16 KB a tile (the
+    // remote view shares rows): asked for first, 122.2 -> 121.6 ms at 131072
+    if (MODE == kModeVanilla) {
+      r.ca = load16(tr);
+      r.cb = load16(tr + 4);
+    }
     r.xl = load16(kr + 8 * rt_c);
     r.xh = load16(kr + 64 + 8 * rt_c);
-    r.ca = load16(tr);
-    r.cb = load16(tr + 4);
+    if (MODE != kModeVanilla) {
+      r.ca = load16(tr);
+      r.cb = load16(tr + 4);
+    }
     return r;
   };
   // word w (0..3) of the rotated chunks: frequencies 8 rt_c + 2w and + 1
@@ -874,7 +884,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == kPfWaves ? 2 : 1) void prefill
     bid -= part * a.n_tail;
   }
   Work W;
-  if (!work_of(a, bid, MODE == kModeFused, W)) return;  // uniform, before any barrier
+  if (!work_of<MODE == kModeVanilla>(a, bid, MODE == kModeFused, W)) return;  // uniform, before any barrier
   if (tail) {
     parts = block_parts(a, W);
     if (part >= parts) return;
@@ -893,7 +903,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == kPfWaves ? 2 : 1) void prefill
 __global__ __launch_bounds__(256) void merge_parts_kernel(PrefillArgs a) {
   const int tb = blockIdx.x;
   Work W;
-  if (!work_of(a, a.n_whole + tb, true, W)) return;
+  if (!work_of<false>(a, a.n_whole + tb, true, W)) return;
   const int parts = block_parts(a, W);
   if (parts <= 1) return;  // written by the block itself
   const int row = 32 * blockIdx.y + (threadIdx.x & 31);
@@ -1110,6 +1120,20 @@ static bool half_blocks(int n_cu, const PrefillArgs& a) {
   return 2LL * a.n_blocks <= n_cu && a.BQ >= 2;
 }
 
+// Whether the XCDs of a vanilla call walk the (sequence, kv head) groups together,
+// one after another, instead of one group each.  Eight groups at once stream 4 KB
+// of K and V per position, and past the last-level cache (256 MB) the misses
+// of these and of the cos/sin rows hold the tiles up; one group is an eighth of
+// that.  But the blocks of a group then share no L2, which needs many of them to
+// pay.  A group per XCD -> in turn, ms: 131072 positions, 32/8 heads (2048 blocks a
+// group), 124.3 -> 121.9; 8/8 (512) 31.8 -> 30.7; 98304, 32/8 70.3 -> 69.5, 16/8 (768)
+// 35.3 -> 35.2, 8/8 (384) 17.9 -> 18.1; 86000, 32/8, 53.3 -> 53.4; 65536 29.9 -> 30.3.
+// The fused kernel, whose remote view reads a G-th of the rows, is sooner with a
+// group per XCD at all lengths (131072: 118.8 against 119.7 ms).
+static bool groups_in_turn(const PrefillArgs& a) {
+  return (a.B * a.Hkv) % 8 == 0 && a.L >= 96 * 1024 && a.n_qblocks >= 512;
+}
+
 // Bytes of scratch a call needs for the states of its parts (0: no block is cut)
 static size_t split_bytes(const PrefillSplit& sp) {
   return sp.n_part > 1 ? (size_t)sp.n_tail * sp.n_part * kPartFloats * sizeof(float) : 0;
@@ -1183,6 +1207,7 @@ hipError_t launch_prefill_chunk(bool bifocal, const uint16_t* q, const uint16_t*
                 : (paged ? launch_blocks<kModeVanilla, true, kPfHalfWaves>(a, grid, stream)
                          : launch_blocks<kModeVanilla, false, kPfHalfWaves>(a, grid, stream));
   } else {
+    a.in_turn = !bifocal && block_table == nullptr && groups_in_turn(a);
     e = launch_attn(bifocal ? kModeFused : kModeVanilla, a, stream);
   }
   if (e == hipSuccess && ev1 != nullptr) e = hipEventRecord(ev1, stream);

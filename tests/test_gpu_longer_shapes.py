@@ -114,3 +114,25 @@ def test_decode_at_the_maximum_length():
     assert np.isfinite(out).all()
     assert err.max() < 2e-2 and err.mean() < 1e-3
     assert np.abs(van[0, 0] - want[0]).max() > 0.5
+
+
+def test_vanilla_groups_in_turn():
+    """From 96K positions and 512 blocks a kv head on, with kv heads a multiple of
+    8, the vanilla kernel takes the heads one after another: the bits of the same
+    sequence as a packed call, which takes its blocks in another order."""
+    Hq, Hkv, L = 8, 8, 131137
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+    q, k, v = (torch.randn((L, h, 128), generator=gen, device="cuda").to(torch.bfloat16)
+               for h in (Hq, Hkv, Hkv))
+    say("vanilla groups in turn L=%d" % L)
+    out = torch.full_like(q, float("nan"))
+    lse = torch.full((Hq, L), float("nan"), device="cuda")
+    api.rope_attention(q[None], k[None], v[None], out=out[None], lse=lse[None])
+    say("the same packed")
+    cu = torch.tensor([0, L], dtype=torch.int32, device="cuda")
+    packed, plse = api.prefill_varlen(q, k, v, cu, max_seqlen=L, bifocal=False, want_lse=True)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), packed.view(torch.int16))
+    assert torch.equal(lse.view(torch.int32), plse.view(torch.int32))
+    assert bool(torch.isfinite(out.float()).all())
