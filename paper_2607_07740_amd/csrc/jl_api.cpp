@@ -309,7 +309,10 @@ int get_scratch(hipStream_t stream, size_t bytes, void** out) {
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cs) != hipSuccess) (void)hipGetLastError();
+  if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {  // the null stream beside a capture
+    (void)hipGetLastError();
+    cs = hipStreamCaptureStatusNone;
+  }
   const bool capturing = cs != hipStreamCaptureStatusNone;
   std::lock_guard<std::mutex> lock(g_mu);
   Scratch* found = nullptr;
